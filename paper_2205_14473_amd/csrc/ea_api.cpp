@@ -304,21 +304,11 @@ struct PtrCheck {
     }
 };
 
-// Vector path when every float row is 16-byte aligned.
-bool vec_ok(int64_t d, std::initializer_list<const void*> ptrs)
-{
-    if (d % 4) return false;
-    for (const void* q : ptrs)
-        if (q && !aligned(q, 16)) return false;
-    return true;
-}
-
 // One fused round.  With t_dev the step is read on the device, lr and beta2
 // come from the schedule at that step, and t_dev is advanced afterwards.
 int step_impl(const char* name, const ea_config_t* c, int64_t t, uint32_t* t_dev, const ea_schedule_t* sched,
               const float* g, float* e_w, float* m_w, float* v_w, float* m, float* v, float* e_s, float* x,
-              uint64_t* wcodes, float* wscales, uint64_t* scodes, float* sscales, void* workspace, void* stream,
-              bool side_stream = true)
+              uint64_t* wcodes, float* wscales, uint64_t* scodes, float* sscales, void* workspace, void* stream)
 {
     Plan p;
     int rc = make_plan(c, &p);
@@ -368,21 +358,17 @@ int step_impl(const char* name, const ea_config_t* c, int64_t t, uint32_t* t_dev
         a.spart = (double*)((char*)workspace + p.off_spart);
         a.ubuf = (float*)((char*)workspace + p.off_ubuf);
     }
-    // Messages sent as raw values are written as float4 by whole-tile kernels.
-    const bool vec = vec_ok(c->d, {g, e_w, a.m_w, a.v_w, a.m, a.v, e_s, x, a.ubuf,
-                                   c->qw.kind == EA_Q_NONE ? (const void*)wcodes : nullptr,
-                                   c->qs.kind == EA_Q_NONE ? (const void*)scodes : nullptr});
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     if (p.wglobal) {
-        e = ea::launch_worker_partials(a, p.C, vec, 0, c->N, s);
+        e = ea::launch_worker_partials(a, p.C, 0, c->N, s);
         if (e == hipSuccess)
             e = ea::launch_finalize(a.wpart, p.ntiles, p.qw.norm, c->d, wscales, p.qw.nscales, c->N, s);
     }
-    if (e == hipSuccess) e = ea::launch_step(a, p.C, vec, s, side_stream);
+    if (e == hipSuccess) e = ea::launch_step(a, p.C, s);
     if (e == hipSuccess && p.sglobal) {
         e = ea::launch_finalize(a.spart, p.ntiles, p.qs.norm, c->d, sscales, 1, 1, s);
-        if (e == hipSuccess) e = ea::launch_server(a, p.C, vec, s);
+        if (e == hipSuccess) e = ea::launch_server(a, p.C, s);
     }
     if (e == hipSuccess && t_dev) e = ea::launch_advance(t_dev, s);
     return hip_status(e, name);
@@ -512,15 +498,14 @@ int ea_worker_compress(const ea_config_t* c, int32_t i, int64_t t, const float* 
     a.wcodes = codes;
     a.wscales = scales;
     a.worker = i;
-    const bool vec = vec_ok(c->d, {g, e_w, a.m_w, a.v_w});
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     if (p.wglobal) {
         a.wpart = (double*)((char*)workspace + p.off_wpart);
-        e = ea::launch_worker_partials(a, p.C, vec, i, i + 1, s);
+        e = ea::launch_worker_partials(a, p.C, i, i + 1, s);
         if (e == hipSuccess) e = ea::launch_finalize(a.wpart, p.ntiles, p.qw.norm, c->d, scales, 1, 1, s);
     }
-    if (e == hipSuccess) e = ea::launch_worker(a, p.C, vec, s);
+    if (e == hipSuccess) e = ea::launch_worker(a, p.C, s);
     return hip_status(e, "ea_worker_compress");
 }
 
@@ -545,8 +530,7 @@ int ea_server_aggregate_adam(const ea_config_t* c, int64_t t, const uint64_t* wc
     a.m = srv ? m : nullptr;
     a.v = srv ? v : nullptr;
     a.ubuf = u_out;
-    const bool vec = vec_ok(c->d, {a.m, a.v, u_out});
-    return hip_status(ea::launch_aggregate(a, p.C, vec, (hipStream_t)stream), "ea_server_aggregate_adam");
+    return hip_status(ea::launch_aggregate(a, p.C, (hipStream_t)stream), "ea_server_aggregate_adam");
 }
 
 int ea_server_compress(const ea_config_t* c, int64_t t, const float* u, float* e_s, uint64_t* codes,
@@ -569,15 +553,14 @@ int ea_server_compress(const ea_config_t* c, int64_t t, const float* u, float* e
     a.scodes = codes;
     a.sscales = scales;
     a.apply = 0;
-    const bool vec = vec_ok(c->d, {u, e_s});
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     if (p.sglobal) {
         a.spart = (double*)((char*)workspace + p.off_spart);
-        e = ea::launch_server_partials(a, p.C, vec, s);
+        e = ea::launch_server_partials(a, p.C, s);
         if (e == hipSuccess) e = ea::launch_finalize(a.spart, p.ntiles, p.qs.norm, c->d, scales, 1, 1, s);
     }
-    if (e == hipSuccess) e = ea::launch_server(a, p.C, vec, s);
+    if (e == hipSuccess) e = ea::launch_server(a, p.C, s);
     return hip_status(e, "ea_server_compress");
 }
 
@@ -595,8 +578,7 @@ int ea_worker_apply(const ea_config_t* c, const uint64_t* codes, const float* sc
     a.scodes = const_cast<uint64_t*>(codes);
     a.sscales = const_cast<float*>(scales);
     a.x = x;
-    const bool vec = vec_ok(c->d, {x});
-    return hip_status(ea::launch_apply(a, p.C, vec, (hipStream_t)stream), "ea_worker_apply");
+    return hip_status(ea::launch_apply(a, p.C, (hipStream_t)stream), "ea_worker_apply");
 }
 
 int ea_step(const ea_config_t* c, int64_t t, const float* g, float* e_w, float* m_w, float* v_w, float* m,
@@ -620,9 +602,8 @@ int ea_step_noalloc(const ea_config_t* c, int64_t t, const float* g, float* e_w,
                     (long long)p.ws_bytes, (long long)kScratchBytes);
     void* ws = nullptr;
     if (p.ws_bytes > 0 && (rc = scratch_ptr(&ws))) return rc;
-    // no side stream for the ragged tile: creating one on first use would allocate
     return step_impl("ea_step_noalloc", c, t, nullptr, nullptr, g, e_w, m_w, v_w, m, v, e_s, x, wcodes, wscales,
-                     scodes, sscales, ws, stream, false);
+                     scodes, sscales, ws, stream);
 }
 
 int ea_schedule_at(const ea_config_t* c, const ea_schedule_t* s, int64_t t, float* lr, float* beta2)

@@ -112,6 +112,15 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
     return c;
 }
 
+// The key made opaque at the start of a tile, so that the scalar unit forms the
+// 18 round keys anew for each tile: held across tiles and phases, they pushed
+// other scalars out into vector lanes (62 -> 47 spilled in the BERT-sized
+// round's kernel).
+__device__ __forceinline__ void renew_key(uint32_t& k0, uint32_t& k1)
+{
+    asm volatile("" : "+s"(k0), "+s"(k1));
+}
+
 // 24-bit uniform in [0, 1), exact in binary32.
 __device__ __forceinline__ float u24(uint32_t r)
 {
@@ -220,12 +229,13 @@ __device__ __forceinline__ void partial_add(Partial& a, int norm, float x)
     }
 }
 
-__device__ __forceinline__ void partial_add4(Partial& a, int norm, float4 x, int nvalid)
+// Elements past the vector's end are +0 and leave every partial as it is.
+__device__ __forceinline__ void partial_add4(Partial& a, int norm, float4 x)
 {
-    if (nvalid > 0) partial_add(a, norm, x.x);
-    if (nvalid > 1) partial_add(a, norm, x.y);
-    if (nvalid > 2) partial_add(a, norm, x.z);
-    if (nvalid > 3) partial_add(a, norm, x.w);
+    partial_add(a, norm, x.x);
+    partial_add(a, norm, x.y);
+    partial_add(a, norm, x.z);
+    partial_add(a, norm, x.w);
 }
 
 // Scale of a bucket from its reduced norm (n = elements in the bucket).
@@ -365,79 +375,66 @@ __device__ __forceinline__ float deq_of(const QDev& q, const float* lut, uint32_
 }
 
 // ---------------------------------------------------------------------------
-// Vector access with tail masking.  VEC: rows are 16-byte aligned.  FULL:
-// the float4 lies inside the vector (no checks).
-// ---------------------------------------------------------------------------
+// Vector access.  Every row is read and written through a raw buffer
+// descriptor over the elements the wave's span has in the vector: lane l of
+// chunk c accesses the 16 bytes at element 256c + 4l of the span, elements
+// past the descriptor read as zero and are not written (the range check is
+// per dword), and 4-byte alignment is enough.  So one code path takes aligned
+// and unaligned rows, whole and ragged tiles, with the base address in scalar
+// registers and the lane offset shared by all rows.  Measured against the two
+// paths it replaced (global accesses: 16-byte ones for whole tiles of aligned
+// rows, else four 4-byte ones per lane with a compare each; the ragged last
+// tile in a launch of its own): see step_kernel.
+//
 // Every vector the round touches is streamed once per round and is far larger
 // than the caches, so loads and stores carry the non-temporal hint.
-#ifndef EA_NONTEMPORAL
-#define EA_NONTEMPORAL 1
-#endif
-typedef float ea_f4v __attribute__((ext_vector_type(4)));
+// ---------------------------------------------------------------------------
+typedef uint32_t ea_u2v __attribute__((ext_vector_type(2)));
+typedef uint32_t ea_u4v __attribute__((ext_vector_type(4)));
+constexpr int kNonTemporal = 2;          // cache policy bits of the buffer builtins
+constexpr int kRawBuffer = 0x00027000;   // descriptor word 3 of a raw buffer
 
-__device__ __forceinline__ float4 ldv(const float* p)
+// A span of a row: the descriptor of elements [base, min(base + span, d)).
+struct Row {
+    __amdgpu_buffer_rsrc_t r;
+};
+
+// Elements of [base, base + span) that lie in a vector of d elements.
+__device__ __forceinline__ int span_left(int64_t base, int64_t d, int span)
 {
-#if EA_NONTEMPORAL
-    const ea_f4v v = __builtin_nontemporal_load(reinterpret_cast<const ea_f4v*>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-#else
-    return *reinterpret_cast<const float4*>(p);
-#endif
+    const int64_t r = d - base;
+    return r <= 0 ? 0 : (r < span ? (int)r : span);
 }
 
-__device__ __forceinline__ void stv(float* p, float4 v)
+// p: start of the row's span; left: its elements.  Both must be wave-uniform.
+__device__ __forceinline__ Row row_of(const float* p, int left)
 {
-#if EA_NONTEMPORAL
-    const ea_f4v w = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(w, reinterpret_cast<ea_f4v*>(p));
-#else
-    *reinterpret_cast<float4*>(p) = v;
-#endif
+    return Row{__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, left * 4, kRawBuffer)};
 }
 
-template <class T>
-__device__ __forceinline__ T ld1(const T* p)
+// Chunk `ch` of the span, this lane's four elements.
+__device__ __forceinline__ float4 ld4(const Row& row, int ch)
 {
-#if EA_NONTEMPORAL
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
+    const ea_u4v v = __builtin_amdgcn_raw_buffer_load_b128(row.r, lane_id() * 16 + ch * (kChunk * 4), 0, kNonTemporal);
+    return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 
-template <class T>
-__device__ __forceinline__ void st1(T* p, T v)
+__device__ __forceinline__ void st4(const Row& row, int ch, float4 v)
 {
-#if EA_NONTEMPORAL
-    __builtin_nontemporal_store(v, p);
-#else
-    *p = v;
-#endif
+    const ea_u4v w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+    __builtin_amdgcn_raw_buffer_store_b128(w, row.r, lane_id() * 16 + ch * (kChunk * 4), 0, kNonTemporal);
 }
 
-template <bool VEC, bool FULL = false>
-__device__ __forceinline__ float4 ld4(const float* __restrict__ p, int64_t n, int64_t lim)
+// A value every lane holds identically, made visibly wave-uniform.
+__device__ __forceinline__ int uniform(int v)
 {
-    if (FULL || (VEC && n + 4 <= lim)) return ldv(p + n);
-    float4 r = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (n < lim) r.x = ld1(p + n);
-    if (n + 1 < lim) r.y = ld1(p + n + 1);
-    if (n + 2 < lim) r.z = ld1(p + n + 2);
-    if (n + 3 < lim) r.w = ld1(p + n + 3);
-    return r;
+    return __builtin_amdgcn_readfirstlane(v);
 }
 
-template <bool VEC, bool FULL = false>
-__device__ __forceinline__ void st4(float* __restrict__ p, int64_t n, int64_t lim, float4 v)
+// This thread's wave in its block.
+__device__ __forceinline__ int wave_id()
 {
-    if (FULL || (VEC && n + 4 <= lim)) {
-        stv(p + n, v);
-        return;
-    }
-    if (n < lim) st1(p + n, v.x);
-    if (n + 1 < lim) st1(p + n + 1, v.y);
-    if (n + 2 < lim) st1(p + n + 2, v.z);
-    if (n + 3 < lim) st1(p + n + 3, v.w);
+    return uniform((int)(threadIdx.x / kWave));
 }
 
 __device__ __forceinline__ float comp(const float4& v, int k)
@@ -478,11 +475,13 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m)
 extern "C" __device__ int ea_writelane_i32(int value, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 // Collects 64-bit ballot words into lanes (word j of a group of 64 lands in
-// lane j) and writes each full group with one coalesced store.
+// lane j) and writes each full group with one coalesced store.  Words past
+// the message's end (chunks of a ragged tile that lie past d) are not written.
 struct WordSink {
-    uint64_t* __restrict__ out;
+    __amdgpu_buffer_rsrc_t r;            // the message's words of the tiles the sink serves
     uint32_t lo, hi;
     int filled;
+    int done;                            // words written so far
 
     __device__ __forceinline__ void put(uint64_t w)
     {
@@ -493,8 +492,10 @@ struct WordSink {
     __device__ __forceinline__ void flush()
     {
         if (filled == 0) return;
-        if (lane_id() < filled) st1(out + lane_id(), ((uint64_t)hi << 32) | lo);
-        out += filled;
+        const ea_u2v w = {lo, hi};
+        if (lane_id() < filled)
+            __builtin_amdgcn_raw_buffer_store_b64(w, r, (done + lane_id()) * 8, 0, kNonTemporal);
+        done += filled;
         filled = 0;
     }
 };

@@ -16,9 +16,9 @@ template <class QW>
 constexpr HalfKernel half()
 {
     return HalfKernel{1, QW::kind(QDev{}), QW::bits(QDev{}), QW::norm(QDev{}), QW::cpb(QDev{}),
-                      step_kernel<1, true, true, QW, QRt, -1>, kernel_tiles(1, true, -1, true),
-                      worker_kernel<1, true, QW>, aggregate_kernel<1, true, QW>, aggregate_kernel<1, true, QW, true>,
-                      server_kernel<1, true, QW>, apply_kernel<1, true, QW>};
+                      step_kernel<1, QW, QRt, -1>, kernel_tiles(1, -1, true),
+                      worker_kernel<1, QW>, aggregate_kernel<1, QW>,
+                      server_kernel<1, QW>, apply_kernel<1, QW>};
 }
 
 const HalfKernel kHalf[] = {

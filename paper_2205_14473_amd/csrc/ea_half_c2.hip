@@ -16,9 +16,9 @@ template <class QW>
 constexpr HalfKernel half()
 {
     return HalfKernel{2, QW::kind(QDev{}), QW::bits(QDev{}), QW::norm(QDev{}), QW::cpb(QDev{}),
-                      step_kernel<2, true, true, QW, QRt, -1>, kernel_tiles(2, true, -1, true),
-                      worker_kernel<2, true, QW>, aggregate_kernel<2, true, QW>, aggregate_kernel<2, true, QW, true>,
-                      server_kernel<2, true, QW>, apply_kernel<2, true, QW>};
+                      step_kernel<2, QW, QRt, -1>, kernel_tiles(2, -1, true),
+                      worker_kernel<2, QW>, aggregate_kernel<2, QW>,
+                      server_kernel<2, QW>, apply_kernel<2, QW>};
 }
 
 const HalfKernel kHalf[] = {

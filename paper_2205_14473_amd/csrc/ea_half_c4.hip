@@ -16,9 +16,9 @@ template <class QW>
 constexpr HalfKernel half()
 {
     return HalfKernel{4, QW::kind(QDev{}), QW::bits(QDev{}), QW::norm(QDev{}), QW::cpb(QDev{}),
-                      step_kernel<4, true, true, QW, QRt, -1>, kernel_tiles(4, true, -1, true),
-                      worker_kernel<4, true, QW>, aggregate_kernel<4, true, QW>, aggregate_kernel<4, true, QW, true>,
-                      server_kernel<4, true, QW>, apply_kernel<4, true, QW>};
+                      step_kernel<4, QW, QRt, -1>, kernel_tiles(4, -1, true),
+                      worker_kernel<4, QW>, aggregate_kernel<4, QW>,
+                      server_kernel<4, QW>, apply_kernel<4, QW>};
 }
 
 const HalfKernel kHalf[] = {

@@ -16,9 +16,9 @@ template <class QW>
 constexpr HalfKernel half()
 {
     return HalfKernel{8, QW::kind(QDev{}), QW::bits(QDev{}), QW::norm(QDev{}), QW::cpb(QDev{}),
-                      step_kernel<8, true, true, QW, QRt, -1>, kernel_tiles(8, true, -1, true),
-                      worker_kernel<8, true, QW>, aggregate_kernel<8, true, QW>, aggregate_kernel<8, true, QW, true>,
-                      server_kernel<8, true, QW>, apply_kernel<8, true, QW>};
+                      step_kernel<8, QW, QRt, -1>, kernel_tiles(8, -1, true),
+                      worker_kernel<8, QW>, aggregate_kernel<8, QW>,
+                      server_kernel<8, QW>, apply_kernel<8, QW>};
 }
 
 const HalfKernel kHalf[] = {

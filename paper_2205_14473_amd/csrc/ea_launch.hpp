@@ -39,7 +39,7 @@ struct StepArgs {
     double* wpart;            // [N][ntiles] per-tile partial norms (qw one bucket)
     double* spart;            // [ntiles]    per-tile partial norms (qs one bucket)
     float* ubuf;              // [d] server input / aggregate output
-    int64_t tile0, tile1;     // fused round: the launch's tiles [tile0, tile1)
+    int64_t tile0;            // fused round: the launch's first tile
     int32_t worker;           // split calls: worker index (Philox stream)
     int32_t apply;            // server_kernel: also update x
     int32_t one_buffer;       // fused round, more workers than waves: single-buffered handoff
@@ -52,24 +52,21 @@ struct StepArgs {
     int64_t sched_T, sched_period;
 };
 
-// Launchers; C = chunks per tile (1..8), vec = rows are 16-byte aligned.
-// side_stream: the ragged last tile may run on a library-owned stream forked
-// from s and joined back to it (created on first use per device).
-hipError_t launch_step(const StepArgs& a, int C, bool vec, hipStream_t s, bool side_stream = true);
+// Launchers; C = chunks per tile (1..8).
+hipError_t launch_step(const StepArgs& a, int C, hipStream_t s);
 
 // Kernels specialized for the worker quantizer only (kind, code bits, norm
 // and chunks per bucket fixed; the server quantizer and the Adam placement
-// read at run time): the fused round for whole tiles of C = chunks-per-bucket
+// read at run time): the fused round for tiles of C = chunks-per-bucket
 // chunks, and the split calls on the worker side.  One table per C, each
 // compiled in its own translation unit.
 struct HalfKernel {
     int C, wkind, wbits, wnorm, wcpb;
     void (*kernel)(StepArgs);
     int tiles;                // tiles per block
-    void (*worker)(StepArgs);     // split call: one worker's compression (aligned rows)
+    void (*worker)(StepArgs);     // split call: one worker's compression
     void (*aggregate)(StepArgs);  // split call: decode and average of the N messages
-    void (*aggregate_full)(StepArgs);  // the same on tiles that lie wholly inside d
-    // The same quantizer on the server side of the split calls (aligned rows):
+    // The same quantizer on the server side of the split calls:
     void (*server)(StepArgs);     // the server's compression
     void (*apply)(StepArgs);      // x -= the server message
 };
@@ -80,7 +77,6 @@ struct SymKernel {
     int C, kind, bits, norm, cpb;
     void (*kernel)(StepArgs);
     int tiles;
-    void (*edge)(StepArgs);   // the last, partial tile (aligned rows)
 };
 const SymKernel* sym_kernels_c4(int* n);
 const SymKernel* sym_kernels_c8(int* n);
@@ -88,14 +84,14 @@ const HalfKernel* half_kernels_c1(int* n);
 const HalfKernel* half_kernels_c2(int* n);
 const HalfKernel* half_kernels_c4(int* n);
 const HalfKernel* half_kernels_c8(int* n);
-hipError_t launch_worker_partials(const StepArgs& a, int C, bool vec, int i0, int i1, hipStream_t s);
-hipError_t launch_server_partials(const StepArgs& a, int C, bool vec, hipStream_t s);
+hipError_t launch_worker_partials(const StepArgs& a, int C, int i0, int i1, hipStream_t s);
+hipError_t launch_server_partials(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_finalize(const double* part, int64_t ntiles, int32_t norm, int64_t n, float* out,
                            int64_t out_stride, int nvec, hipStream_t s);
-hipError_t launch_worker(const StepArgs& a, int C, bool vec, hipStream_t s);
-hipError_t launch_aggregate(const StepArgs& a, int C, bool vec, hipStream_t s);
-hipError_t launch_server(const StepArgs& a, int C, bool vec, hipStream_t s);
-hipError_t launch_apply(const StepArgs& a, int C, bool vec, hipStream_t s);
+hipError_t launch_worker(const StepArgs& a, int C, hipStream_t s);
+hipError_t launch_aggregate(const StepArgs& a, int C, hipStream_t s);
+hipError_t launch_server(const StepArgs& a, int C, hipStream_t s);
+hipError_t launch_apply(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_fill(float* p, int64_t n, float value, hipStream_t s);
 // t_dev[0] <- t_dev[0] + 1 (after the kernels of a round that read it).
 hipError_t launch_advance(uint32_t* t_dev, hipStream_t s);

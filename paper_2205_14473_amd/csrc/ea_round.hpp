@@ -18,8 +18,11 @@
 //
 // Every kernel is a template over the quantizer traits of both sides and the
 // Adam placement: QRt / placement -1 give the generic kernels used for any
-// configuration, QCt<...> the specialized ones for common shapes.  Tiles
-// that lie wholly inside d go to kernels without per-element bounds checks.
+// configuration, QCt<...> the specialized ones for common shapes.  Every
+// kernel takes whole and ragged tiles of aligned and unaligned rows alike:
+// elements past d read as zero and are not written (Row), and the few places
+// where a zero would matter (codes of 0, the server's sum) are masked under a
+// wave-uniform branch that only ragged tiles take.
 #pragma once
 
 #include "ea_launch.hpp"
@@ -56,8 +59,8 @@ __host__ __device__ constexpr int max_round_waves(int C)
 #define EA_C1_SERVER_WAVES 4
 #endif
 
-// Tiles per block of the fused round.  Lean kernels (whole tiles, Adam at
-// the server) take two consecutive tiles per block; the others one.
+// Tiles per block of the fused round.  Lean kernels (Adam at the server) take
+// two consecutive tiles per block; the others one.
 #ifndef EA_TILES_PER_BLOCK
 #define EA_TILES_PER_BLOCK 2
 #endif
@@ -67,9 +70,8 @@ __host__ __device__ constexpr int round_tiles_per_block(int C, bool lean)
 }
 
 // Minimum waves per SIMD the compiler must leave room for (caps VGPRs).
-// Kernels over whole tiles with Adam at the server have no per-element
-// bounds checks and no worker moments, and need fewer registers than the
-// others.
+// Kernels with Adam at the server have no worker moments and need fewer
+// registers than the others.
 #ifndef EA_C4_MIN_WAVES
 #define EA_C4_MIN_WAVES 1
 #endif
@@ -90,9 +92,9 @@ __host__ __device__ constexpr int round_min_waves(int C, bool lean)
 #ifndef EA_HALF_C1_TILES
 #define EA_HALF_C1_TILES 2
 #endif
-__host__ __device__ constexpr int kernel_tiles(int C, bool full, int pl, bool half)
+__host__ __device__ constexpr int kernel_tiles(int C, int pl, bool half)
 {
-    return half && full && C == 1 ? EA_HALF_C1_TILES : round_tiles_per_block(C, full && pl == AT_SERVER);
+    return half && C == 1 ? EA_HALF_C1_TILES : round_tiles_per_block(C, pl == AT_SERVER);
 }
 template <class QW, class QS, int PL>
 __host__ __device__ constexpr bool half_kernel()
@@ -100,11 +102,18 @@ __host__ __device__ constexpr bool half_kernel()
     return QW::fixed && !QS::fixed && PL < 0;
 }
 
-// Number of valid elements among a lane's float4 at element n.
-__device__ __forceinline__ int nvalid4(int64_t n, int64_t d)
+// Elements of the tile's chunk `ch` among this lane's four that lie inside d
+// (left: the tile's elements inside d).
+__device__ __forceinline__ bool inside(int left, int ch, int k)
 {
-    const int64_t r = d - n;
-    return r <= 0 ? 0 : (r >= 4 ? 4 : (int)r);
+    return ch * kChunk + 4 * lane_id() + k < left;
+}
+
+// Marks a branch that only ragged tiles take: without it the compiler turns
+// the few selects inside into unconditional ones for every tile.
+__device__ __forceinline__ void ragged_only()
+{
+    asm volatile("; ragged tile");
 }
 
 template <int PL>
@@ -146,17 +155,29 @@ __device__ __forceinline__ StepArgs with_step(const StepArgs& in)
 // values.  codes/scales point at the start of the message.  The code words go
 // to `sink`, which the caller opens at the tile's first word (message_sink)
 // and flushes; consecutive tiles may share one sink, since their words are
-// consecutive in the message.
+// consecutive in the message.  left: elements of the tile inside d, or of all
+// the tiles that share the sink.
 // ---------------------------------------------------------------------------
 template <class QT>
-__device__ __forceinline__ WordSink message_sink(const QDev& q, uint64_t* codes, int64_t base)
+__device__ __forceinline__ WordSink message_sink(const QDev& q, uint64_t* codes, int64_t base, int left)
 {
     WordSink sink;
-    sink.out = codes + (base >> 8) * 4 * QT::bits(q);
+    sink.r = __builtin_amdgcn_make_buffer_rsrc(codes + (base >> 8) * 4 * QT::bits(q), 0,
+                                               (left + kChunk - 1) / kChunk * 32 * QT::bits(q), kRawBuffer);
     sink.lo = 0u;
     sink.hi = 0u;
     sink.filled = 0;
+    sink.done = 0;
     return sink;
+}
+
+// Elements inside d of the bucket that starts at chunk b0 of a tile with
+// `left` elements inside d (cpb chunks per bucket, at least 1): 0 when the
+// bucket lies wholly past d.
+__device__ __forceinline__ int bucket_elements(int left, int b0, int cpb)
+{
+    const int r = left - b0 * kChunk, B = cpb * kChunk;
+    return r <= 0 ? 0 : (r < B ? r : B);
 }
 
 // Sparsifier tuning: how many of each lane's largest keys a first threshold
@@ -264,24 +285,30 @@ __device__ __forceinline__ void wave_or_and(uint32_t vo, uint32_t va, uint32_t& 
 // its lane).  The kept
 // values are listed in element order at positions counted the same way.
 // Elements past d get key 0 and the highest indices, so they rank below
-// every element of the vector and are never kept.
+// every element of the vector and are never kept (a bucket wholly past d
+// keeps none: k = 0).
 //
 // FLAGS (random-k on wide tiles, whose keys do not depend on p): only the
 // code words are sent, and the lane's kept flags are returned,
 // bit 4j + k for its element in chunk j, slot k; sparse_values then writes
 // the values from p, which is not read here.
-template <int C, bool FULL, class QT, bool FLAGS = false>
-__device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&p)[C], int64_t base, int nch,
-                                                  int64_t d, uint32_t k0, uint32_t k1, uint32_t step, uint32_t sid,
-                                                  float* __restrict__ vals, WordSink& sink, float4 (&deq)[C])
+// keys_done is called once the keys are formed, before the selection.
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int C, class QT, bool FLAGS = false, class KeysDone = Nothing>
+__device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&p)[C], int64_t base, int left,
+                                                  uint32_t k0, uint32_t k1, uint32_t step, uint32_t sid,
+                                                  float* __restrict__ vals, WordSink& sink, float4 (&deq)[C],
+                                                  const KeysDone& keys_done = KeysDone())
 {
     static_assert(!FLAGS || (C >= 4 && QT::fixed && QT::kind(QDev{}) == Q_RANDK), "flags first: wide random-k only");
     uint32_t kbits_out = 0u;
+    renew_key(k0, k1);
     const int lane = lane_id();
     const int cpb = QT::cpb(q);
     const bool topk = QT::kind(q) == Q_TOPK;
     const int top = topk ? 31 : 23;   // keys below 2^31 (TOPK) or 2^24 (RANDK)
-    if (FULL) nch = C;
 
     // On tiles of 4 or more chunks a top-k key fixed at compile time is
     // formed from p where it is used (one AND), so the tile's keys take no
@@ -293,27 +320,29 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
     for (int ch = 0; ch < C; ++ch) {
         deq[ch] = zero4();
         if constexpr (!kKeyOfP) {
-            const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-            const int nv = FULL ? 4 : (ch < nch ? nvalid4(n, d) : 0);
             uint4 r = make_uint4(0u, 0u, 0u, 0u);
-            if (!topk && (FULL || ch < nch)) {
-                const uint64_t j = (uint64_t)n >> 2;
+            if (!topk) {
+                const uint64_t j = (uint64_t)(base + (int64_t)ch * kChunk + 4 * lane) >> 2;
                 r = philox10(make_uint4((uint32_t)j, (uint32_t)(j >> 32), step, sid), k0, k1);
             }
             const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t kv = topk ? (__float_as_uint(comp(p[ch], k)) & 0x7FFFFFFFu) : (rr[k] >> 8);
-                keys[ch][k] = (FULL || k < nv) ? kv : 0u;
+            for (int k = 0; k < 4; ++k)
+                keys[ch][k] = topk ? (__float_as_uint(comp(p[ch], k)) & 0x7FFFFFFFu) : (rr[k] >> 8);
+            // p is +0 past d, so top-k keys are 0 there already
+            if (!topk && left < C * kChunk) {
+                ragged_only();
+#pragma unroll
+                for (int k = 0; k < 4; ++k) keys[ch][k] = inside(left, ch, k) ? keys[ch][k] : 0u;
             }
         }
     }
+    keys_done();
     const auto key = [&](int j, int k) -> uint32_t {
         if constexpr (kKeyOfP) {
             uint32_t kv;
             asm volatile("v_and_b32 %0, 0x7fffffff, %1" : "=v"(kv) : "v"(comp(p[j], k)));
-            if constexpr (FULL) return kv;
-            else return j < nch && k < nvalid4(base + (int64_t)j * kChunk + 4 * lane, d) ? kv : 0u;
+            return kv;
         } else {
             return keys[j][k];
         }
@@ -323,9 +352,7 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
 #pragma unroll
     for (int b0 = 0; b0 < C; ++b0) {
         if ((b0 & (cpb - 1)) != 0) continue;
-        if (!FULL && b0 >= nch) continue;
-        const int64_t e0 = base + (int64_t)b0 * kChunk;
-        const int64_t nb = FULL ? q.B : ((d - e0) < q.B ? (d - e0) : q.B);
+        const int nb = bucket_elements(left, b0, cpb);
         const uint32_t kk = (uint32_t)(nb < q.keep ? nb : q.keep);
 
         // Threshold T: the kk-th largest key of the bucket.
@@ -467,7 +494,6 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
 #pragma unroll
             for (int j = 0; j < C; ++j) {
                 if (j < b0 || j >= b0 + cpb) continue;
-                if (!FULL && j >= nch) continue;
                 uint64_t km[4];
                 uint32_t below = 0, tot = 0;
 #pragma unroll
@@ -493,15 +519,12 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
             // Chunk by chunk, each chunk's flags just before its output (the
             // same steps; the output loop is written out in both branches
             // because sharing it measured slower on these tiles: random-64 of
-            // 2048 5.7 -> 6.4 ms).  Chunks past d come last in element
-            // order, so skipping them leaves the ranks of the others as they
-            // are.
+            // 2048 5.7 -> 6.4 ms).
             const uint32_t need = exact ? 0u : need_of();
             uint32_t eq_before = 0, kept_before = 0;
 #pragma unroll
             for (int j = 0; j < C; ++j) {
                 if (j < b0 || j >= b0 + cpb) continue;
-                if (!FULL && j >= nch) continue;
                 bool kept[4];
                 if (exact) {
 #pragma unroll
@@ -556,7 +579,7 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
             }
         }
         // A bucket shorter than keep: the remaining value slots are zero.
-        if (!FULL && !FLAGS)
+        if (!FLAGS && nb > 0 && nb < q.keep)
             for (uint32_t sl = kk + (uint32_t)lane; sl < (uint32_t)q.keep; sl += kWave) vb[sl] = 0.0f;
     }
     return kbits_out;
@@ -567,29 +590,25 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
 // which has sent the code words): per bucket the kept values in element
 // order, zeros in the value slots past a short bucket's kk, and the
 // dequantized tile.
-template <int C, bool FULL, class QT>
+template <int C, class QT>
 __device__ __forceinline__ void sparse_values(const QDev& q, const float4 (&p)[C], uint32_t kbits, int64_t base,
-                                              int nch, int64_t d, float* __restrict__ vals, float4 (&deq)[C])
+                                              int left, float* __restrict__ vals, float4 (&deq)[C])
 {
     const int lane = lane_id();
     const int cpb = QT::cpb(q);
-    if (FULL) nch = C;
     const int64_t chunk0 = base >> 8;
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) deq[ch] = zero4();
 #pragma unroll
     for (int b0 = 0; b0 < C; ++b0) {
         if ((b0 & (cpb - 1)) != 0) continue;
-        if (!FULL && b0 >= nch) continue;
-        const int64_t e0 = base + (int64_t)b0 * kChunk;
-        const int64_t nb = FULL ? q.B : ((d - e0) < q.B ? (d - e0) : q.B);
+        const int nb = bucket_elements(left, b0, cpb);
         const uint32_t kk = (uint32_t)(nb < q.keep ? nb : q.keep);
         float* vb = vals + ((chunk0 + b0) >> QT::cpb_shift(q)) * (int64_t)q.keep;
         uint32_t kept_before = 0;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             if (j < b0 || j >= b0 + cpb) continue;
-            if (!FULL && j >= nch) continue;
             uint32_t below = 0, tot = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -609,7 +628,7 @@ __device__ __forceinline__ void sparse_values(const QDev& q, const float4 (&p)[C
             }
             kept_before += tot;
         }
-        if (!FULL)
+        if (nb > 0 && nb < q.keep)
             for (uint32_t sl = kk + (uint32_t)lane; sl < (uint32_t)q.keep; sl += kWave) vb[sl] = 0.0f;
     }
 }
@@ -628,15 +647,17 @@ __host__ __device__ constexpr bool select_first()
     return C >= EA_SELECT_FIRST_MIN_C && QT::fixed && QT::kind(QDev{}) == Q_RANDK;
 }
 
-template <int C, bool FULL, class QT>
+// p is +0 past d (left: the tile's elements inside d); what deq holds there
+// is not defined.
+template <int C, class QT>
 __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, const float4 (&p)[C],
-                                              int64_t base, int nch, int64_t d, uint32_t k0, uint32_t k1,
+                                              int64_t base, int left, uint32_t k0, uint32_t k1,
                                               uint32_t step, uint32_t sid, float given_scale,
                                               uint64_t* __restrict__ codes, float* __restrict__ scales,
                                               WordSink& sink, float4 (&deq)[C])
 {
     if (is_sparse<QT>(q)) {
-        sparsify_tile<C, FULL, QT>(q, p, base, nch, d, k0, k1, step, sid, scales, sink, deq);
+        sparsify_tile<C, QT>(q, p, base, left, k0, k1, step, sid, scales, sink, deq);
         return;
     }
     const int lane = lane_id();
@@ -644,7 +665,8 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
     const int norm = QT::norm(q);
     const int cpb = QT::cpb(q);
     const int bits = QT::bits(q);
-    if (FULL) nch = C;
+    const bool ragged = left < C * kChunk;
+    renew_key(k0, k1);
 
     const int64_t chunk0 = base >> 8;   // first chunk of the tile (tiles start on bucket boundaries)
     float s[C];
@@ -658,35 +680,29 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
             for (int ch = 0; ch < C; ++ch) {
                 part[ch].sum = 0.0;
                 part[ch].mx = 0.0f;
-                if (ch < nch)
-                    partial_add4(part[ch], norm, p[ch], FULL ? 4 : nvalid4(base + ch * kChunk + 4 * lane, d));
+                partial_add4(part[ch], norm, p[ch]);
             }
 #pragma unroll
             for (int ch = 0; ch < C; ++ch) {
                 if ((ch & (cpb - 1)) == 0) {
-                    if (ch < nch) {
-                        Partial tot;
-                        tot.sum = 0.0;
-                        tot.mx = 0.0f;
+                    Partial tot;
+                    tot.sum = 0.0;
+                    tot.mx = 0.0f;
 #pragma unroll
-                        for (int j = 0; j < C; ++j) {
-                            if (j >= ch && j < ch + cpb) {
-                                tot.sum += part[j].sum;
-                                tot.mx = fmaxf(tot.mx, part[j].mx);
-                            }
+                    for (int j = 0; j < C; ++j) {
+                        if (j >= ch && j < ch + cpb) {
+                            tot.sum += part[j].sum;
+                            tot.mx = fmaxf(tot.mx, part[j].mx);
                         }
-                        const int64_t b0 = base + (int64_t)ch * kChunk;
-                        const int64_t nb = FULL ? q.B : ((d - b0) < q.B ? (d - b0) : q.B);
-                        const double S = norm == S_MAX ? 0.0 : wave_sum(tot.sum);
-                        const float M = norm == S_MAX ? wave_max(tot.mx) : 0.0f;
-                        s[ch] = scale_from(norm, S, M, nb);
-                        // A plain store: the caches merge the 4-byte scales of
-                        // neighbouring tiles, where streaming stores reach HBM
-                        // one partial line at a time.
-                        if (lane == 0) scales[(chunk0 + ch) >> QT::cpb_shift(q)] = s[ch];
-                    } else {
-                        s[ch] = 0.0f;
                     }
+                    const int nb = bucket_elements(left, ch, cpb);
+                    const double S = norm == S_MAX ? 0.0 : wave_sum(tot.sum);
+                    const float M = norm == S_MAX ? wave_max(tot.mx) : 0.0f;
+                    s[ch] = scale_from(norm, S, M, nb);
+                    // A plain store: the caches merge the 4-byte scales of
+                    // neighbouring tiles, where streaming stores reach HBM
+                    // one partial line at a time.
+                    if (lane == 0 && nb > 0) scales[(chunk0 + ch) >> QT::cpb_shift(q)] = s[ch];
                 } else {
                     s[ch] = s[ch > 0 ? ch - 1 : 0];
                 }
@@ -699,15 +715,11 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
 
     const bool gated = scale_gated<QT>(q);
     if (kind == Q_NONE) {
-        // Whole tiles: the raw message is 16-byte aligned (the launcher
-        // requires it of messages sent as values before it takes them).
-        float* raw = reinterpret_cast<float*>(codes);
+        const Row raw = row_of(reinterpret_cast<float*>(codes) + base, left);
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) {
             deq[ch] = p[ch];
-            const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-            if (FULL) st4<true, true>(raw, n, d, p[ch]);
-            else if (ch < nch) st4<false>(raw, n, d, p[ch]);
+            st4(raw, ch, p[ch]);
         }
         return;
     }
@@ -722,8 +734,6 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
     bool ok = true, tiny = false;
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-        const int nv = FULL ? 4 : (ch < nch ? nvalid4(n, d) : 0);
         if (ch == 0 || (cpb != 0 && (ch & (cpb - 1)) == 0)) {
             sc = uniform(s[ch]);
             ok = !gated || (sc > 0.0f && !isinf(sc));
@@ -735,19 +745,17 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
             // sent as zero codes and dequantizes to zero.
             const uint32_t zc = zero_code_of<QT>(q);
             deq[ch] = zero4();
-            if (FULL || ch < nch) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool valid = FULL || k < nv;
-                    for (int pl = 0; pl < bits; ++pl)
-                        sink.put(__builtin_amdgcn_ballot_w64(valid && ((zc >> pl) & 1u) != 0u));
-                }
+            for (int k = 0; k < 4; ++k) {
+                const bool valid = inside(left, ch, k);
+                for (int pl = 0; pl < bits; ++pl)
+                    sink.put(__builtin_amdgcn_ballot_w64(valid && ((zc >> pl) & 1u) != 0u));
             }
             continue;
         }
         uint4 r = make_uint4(0u, 0u, 0u, 0u);
-        if (kind == Q_STOCH && (FULL || ch < nch)) {
-            const uint64_t j = (uint64_t)n >> 2;
+        if (kind == Q_STOCH) {
+            const uint64_t j = (uint64_t)(base + (int64_t)ch * kChunk + 4 * lane) >> 2;
             r = philox10(make_uint4((uint32_t)j, (uint32_t)(j >> 32), step, sid), k0, k1);
         }
         const uint32_t rr[4] = {r.x, r.y, r.z, r.w};
@@ -760,25 +768,23 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
             for (int k = 0; k < 4; ++k) cc[k] = code_of<QT>(q, comp(p[ch], k), inv, rr[k]);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float x = comp(p[ch], k);
-            float dv = deq_of<QT>(q, lut, cc[k], x, sc);
-            if (!FULL && k >= nv) {
-                cc[k] = 0u;
-                dv = 0.0f;
-            }
-            set_comp(deq[ch], k, dv);
-            if (FULL || ch < nch) {
-                if constexpr (QT::fixed) {
-                    // Codes are below 2^bits, so the top plane is a compare.
+        for (int k = 0; k < 4; ++k) set_comp(deq[ch], k, deq_of<QT>(q, lut, cc[k], comp(p[ch], k), sc));
+        // The code of 0 need not be 0 (it is for signs).
+        if (kind != Q_SCALED_SIGN && ragged) {
+            ragged_only();
 #pragma unroll
-                    for (int pl = 0; pl < QT::bits(q); ++pl)
-                        sink.put(__builtin_amdgcn_ballot_w64(pl == QT::bits(q) - 1 ? cc[k] >= (1u << pl)
-                                                                                    : ((cc[k] >> pl) & 1u) != 0u));
-                } else {
-                    for (int pl = 0; pl < bits; ++pl)
-                        sink.put(__builtin_amdgcn_ballot_w64(((cc[k] >> pl) & 1u) != 0u));
-                }
+            for (int k = 0; k < 4; ++k) cc[k] = inside(left, ch, k) ? cc[k] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (QT::fixed) {
+                // Codes are below 2^bits, so the top plane is a compare.
+#pragma unroll
+                for (int pl = 0; pl < QT::bits(q); ++pl)
+                    sink.put(__builtin_amdgcn_ballot_w64(pl == QT::bits(q) - 1 ? cc[k] >= (1u << pl)
+                                                                                : ((cc[k] >> pl) & 1u) != 0u));
+            } else {
+                for (int pl = 0; pl < bits; ++pl) sink.put(__builtin_amdgcn_ballot_w64(((cc[k] >> pl) & 1u) != 0u));
             }
         }
     }
@@ -800,12 +806,10 @@ __host__ __device__ constexpr int max_code_bits()
 // for lanes 32-63; of each chunk's 4*bits words, lane l holds that half of
 // word l mod 32 (x[ch][0]) and, for codes wider than 8 bits, of word
 // 32 + l mod 32 (x[ch][1]).  Written to LDS in that order, the halves a
-// lane needs are consecutive (decode_words).  Lanes past a chunk's words, and
-// chunks past the tile's end, load a word that exists and decode to nothing:
+// lane needs are consecutive (decode_words).  Lanes past a chunk's words load
+// its last word, and chunks past d read as zero (nothing past d is stored):
 // the loads take no branch, so the next worker's words stay in flight while
-// the current worker's are decoded.  (The select on the chunk count also
-// keeps the compiler from moving a prefetch's load into the next iteration,
-// where it would be waited for at once.)
+// the current worker's are decoded.
 template <int C, class QT>
 struct CodeWords {
     static constexpr int R = max_code_bits<QT>() > 8 ? 2 : 1;
@@ -814,35 +818,37 @@ struct CodeWords {
 
 template <int C, class QT>
 __device__ __forceinline__ void load_code_words(const QDev& q, const uint64_t* __restrict__ codes, int64_t base,
-                                                int nch, CodeWords<C, QT>& w)
+                                                int left, CodeWords<C, QT>& w)
 {
     const int lane = lane_id();
     const int nw = 4 * QT::bits(q);
-    const uint32_t* __restrict__ c32 = reinterpret_cast<const uint32_t*>(codes);
+    const int words = (left + kChunk - 1) / kChunk * nw;
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint64_t*>(codes) + (base >> 8) * nw, 0, words * 8, kRawBuffer);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t chunk = (base >> 8) + (ch < nch ? ch : nch - 1);
 #pragma unroll
-        for (int r = 0; r < CodeWords<C, QT>::R; ++r) {
-            const int j = 32 * r + (lane & 31);
-            const uint32_t v = c32[(chunk * nw + (j < nw ? j : nw - 1)) * 2 + (lane >> 5)];
-            w.x[ch][r] = ch < nch ? v : 0u;
+        for (int h = 0; h < CodeWords<C, QT>::R; ++h) {
+            const int j = 32 * h + (lane & 31);
+            w.x[ch][h] = __builtin_amdgcn_raw_buffer_load_b32(r, (j < nw ? j : nw - 1) * 8 + (lane >> 5) * 4 + ch * nw * 8,
+                                                              0, 0);
         }
     }
 }
 
-// The scale of each chunk's bucket (1 for kinds without scales).
+// The scale of each chunk's bucket (1 for kinds without scales); chunks past
+// d take the last chunk's.
 template <int C, class QT>
 __device__ __forceinline__ void load_chunk_scales(const QDev& q, const float* __restrict__ scales, int64_t base,
-                                                  int nch, float (&sc)[C])
+                                                  int left, float (&sc)[C])
 {
+    const int nch = (left + kChunk - 1) / kChunk;
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
         sc[ch] = 1.0f;
         if (has_scale<QT>(q)) {
             const int64_t chunk = (base >> 8) + (ch < nch ? ch : nch - 1);
-            const float v = scales[QT::cpb(q) == 0 ? 0 : (chunk >> QT::cpb_shift(q))];
-            sc[ch] = ch < nch ? v : 1.0f;
+            sc[ch] = scales[QT::cpb(q) == 0 ? 0 : (chunk >> QT::cpb_shift(q))];
         }
     }
 }
@@ -890,7 +896,7 @@ __host__ __device__ constexpr uint32_t dot_weights(int k, int i, bool hi)
 // into its byte offset in the code table.
 template <int C, class QT, bool SUM, bool SCALED = false>
 __device__ __forceinline__ void decode_words_rows(const QDev& q, const float* lut, const CodeWords<C, QT>& w,
-                                                  const float (&scs)[C], int64_t base, int nch, int64_t d,
+                                                  const float (&scs)[C],
                                                   uint32_t* stage, float4 (&deq)[C], float* stab = nullptr)
 {
     constexpr int R = CodeWords<C, QT>::R;
@@ -930,10 +936,8 @@ __device__ __forceinline__ void decode_words_rows(const QDev& q, const float* lu
     const int bl = lane & 7;
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
         const float sc = uniform(scs[ch]);
-        const bool ok = ch < nch && (!scale_gated<QT>(q) || (sc > 0.0f && !isinf(sc)));
-        const int nv = nvalid4(n, d);
+        const bool ok = !scale_gated<QT>(q) || (sc > 0.0f && !isinf(sc));
         const float se = ok ? sc : 0.0f;
         // the lane's row: B dwords of four word-bytes each, reduced to the
         // lane's bit of each byte
@@ -963,7 +967,7 @@ __device__ __forceinline__ void decode_words_rows(const QDev& q, const float* lu
             const int kind = QT::kind(q);
             const float s = SUM ? se : sc;
             const float dv = SCALED ? tv : kind == Q_SCALED_SIGN ? (c4 ? -s : s) : (kind == Q_POW2 ? tv : s * tv);
-            set_comp(deq[ch], k, SUM || (ok && k < nv) ? dv : 0.0f);
+            set_comp(deq[ch], k, SUM || ok ? dv : 0.0f);
         }
     }
 }
@@ -975,13 +979,13 @@ __device__ __forceinline__ void decode_words_rows(const QDev& q, const float* lu
 // moves each bit to its place in the code.  One wave's LDS accesses complete
 // in order, so only the compiler has to be kept from reordering them.
 //
-// SUM: the caller only adds the values to sums that start at +0 and never
-// stores the lanes past d.  A gated bucket (zero or non-finite scale) then
-// decodes to zeros of either sign, which leave such a sum's bits as +0 would,
-// and the lanes past d or past the tile are not masked: no select per element.
+// No caller stores elements past d, and what they decode to is not defined.
+// SUM: the caller only adds the values to sums that start at +0.  A gated
+// bucket (zero or non-finite scale) then decodes to zeros of either sign,
+// which leave such a sum's bits as +0 would: no select per element.
 template <int C, class QT, bool SUM = false, bool SCALED = false>
 __device__ __forceinline__ void decode_words(const QDev& q, const float* lut, const CodeWords<C, QT>& w,
-                                             const float (&scs)[C], int64_t base, int nch, int64_t d,
+                                             const float (&scs)[C],
                                              uint32_t* stage, float4 (&deq)[C], float* stab = nullptr)
 {
     // Byte rows for fixed widths of 2 bits and more; 1-bit codes read their
@@ -989,7 +993,7 @@ __device__ __forceinline__ void decode_words(const QDev& q, const float* lut, co
     // than writing bytes (ResNet-18-sized sign, 2048-element buckets: 58 against
     // 64 us).
     if constexpr (QT::fixed && max_code_bits<QT>() >= 2) {
-        decode_words_rows<C, QT, SUM, SCALED>(q, lut, w, scs, base, nch, d, stage, deq, stab);
+        decode_words_rows<C, QT, SUM, SCALED>(q, lut, w, scs, stage, deq, stab);
         return;
     }
     constexpr int R = CodeWords<C, QT>::R;
@@ -1008,10 +1012,8 @@ __device__ __forceinline__ void decode_words(const QDev& q, const float* lut, co
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
         const float sc = uniform(scs[ch]);
-        const bool ok = ch < nch && (!scale_gated<QT>(q) || (sc > 0.0f && !isinf(sc)));
-        const int nv = nvalid4(n, d);
+        const bool ok = !scale_gated<QT>(q) || (sc > 0.0f && !isinf(sc));
         // this lane's halves of the chunk's words (with the code width known
         // at compile time; else read one at a time below)
         const uint32_t* sl = stage + ch * R * kWave + (lane & 32);
@@ -1042,7 +1044,7 @@ __device__ __forceinline__ void decode_words(const QDev& q, const float* lut, co
             const int kind = QT::kind(q);
             const float s = SUM ? (ok ? sc : 0.0f) : sc;
             const float dv = kind == Q_SCALED_SIGN ? (c4 ? -s : s) : (kind == Q_POW2 ? tv : s * tv);
-            set_comp(deq[ch], k, SUM || (ok && k < nv) ? dv : 0.0f);
+            set_comp(deq[ch], k, SUM || ok ? dv : 0.0f);
         }
     }
 }
@@ -1058,7 +1060,7 @@ __device__ __forceinline__ bool plane_coded(const QDev& q)
 // Dequantize one tile of a message (the inverse of the code table).
 template <int C, class QT>
 __device__ __forceinline__ void dequant_tile(const QDev& q, const float* lut, const uint64_t* __restrict__ codes,
-                                             const float* __restrict__ scales, int64_t base, int nch, int64_t d,
+                                             const float* __restrict__ scales, int64_t base, int left,
                                              uint32_t* stage, float4 (&deq)[C])
 {
     const int lane = lane_id();
@@ -1069,7 +1071,7 @@ __device__ __forceinline__ void dequant_tile(const QDev& q, const float* lut, co
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) {
             deq[ch] = zero4();
-            if (ch >= nch) continue;
+            if (ch * kChunk >= left) continue;
             const int64_t chunk = (base >> 8) + ch;
             if ((chunk & (QT::cpb(q) - 1)) == 0) before = 0;
             const uint64_t* w = codes + chunk * 4;
@@ -1099,16 +1101,14 @@ __device__ __forceinline__ void dequant_tile(const QDev& q, const float* lut, co
     if (plane_coded<QT>(q)) {
         CodeWords<C, QT> wv;
         float sc[C];
-        load_code_words<C, QT>(q, codes, base, nch, wv);
-        load_chunk_scales<C, QT>(q, scales, base, nch, sc);
-        decode_words<C, QT>(q, lut, wv, sc, base, nch, d, stage, deq);
+        load_code_words<C, QT>(q, codes, base, left, wv);
+        load_chunk_scales<C, QT>(q, scales, base, left, sc);
+        decode_words<C, QT>(q, lut, wv, sc, stage, deq);
         return;
     }
+    const Row raw = row_of(reinterpret_cast<const float*>(codes) + base, left);
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-        deq[ch] = ch < nch ? ld4<false>(reinterpret_cast<const float*>(codes), n, d) : zero4();
-    }
+    for (int ch = 0; ch < C; ++ch) deq[ch] = ld4(raw, ch);
 }
 
 // Raw worker rows of one tile.
@@ -1117,25 +1117,37 @@ struct WorkerRows {
     float4 g[C], e[C], m[C], v[C];
 };
 
-template <int C, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void load_worker(const StepArgs& a, const float* __restrict__ g,
-                                            const float* __restrict__ e, const float* __restrict__ mw,
-                                            const float* __restrict__ vw, int64_t base, int nch,
-                                            WorkerRows<C>& r)
+// One worker's rows over a span of elements (the tiles of a block, or one
+// tile).
+struct WorkerSpan {
+    Row g, e, m, v;
+};
+
+template <int PL>
+__device__ __forceinline__ WorkerSpan worker_span(const StepArgs& a, const float* g, const float* e, const float* mw,
+                                                  const float* vw, int64_t base, int left)
 {
-    const int lane = lane_id();
+    WorkerSpan s;
+    s.g = row_of(g + base, left);
+    s.e = row_of(e + base, left);
+    if (placement_of<PL>(a) == AT_WORKER) {
+        s.m = row_of(mw + base, left);
+        s.v = row_of(vw + base, left);
+    }
+    return s;
+}
+
+// The tile that starts at chunk ch0 of the span.
+template <int C, int PL>
+__device__ __forceinline__ void load_worker(const StepArgs& a, const WorkerSpan& s, int ch0, WorkerRows<C>& r)
+{
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-        if (!FULL && ch >= nch) {
-            r.g[ch] = r.e[ch] = r.m[ch] = r.v[ch] = zero4();
-            continue;
-        }
-        r.g[ch] = ld4<VEC, FULL>(g, n, a.d);
-        r.e[ch] = ld4<VEC, FULL>(e, n, a.d);
+        r.g[ch] = ld4(s.g, ch0 + ch);
+        r.e[ch] = ld4(s.e, ch0 + ch);
         if (placement_of<PL>(a) == AT_WORKER) {
-            r.m[ch] = ld4<VEC, FULL>(mw, n, a.d);
-            r.v[ch] = ld4<VEC, FULL>(vw, n, a.d);
+            r.m[ch] = ld4(s.m, ch0 + ch);
+            r.v[ch] = ld4(s.v, ch0 + ch);
         }
     }
 }
@@ -1223,18 +1235,15 @@ __device__ __forceinline__ void worker_p(const StepArgs& a, WorkerRows<C>& r, fl
     }
 }
 
-template <int C, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void store_moments(const StepArgs& a, float* __restrict__ mw, float* __restrict__ vw,
-                                              int64_t base, int nch, const WorkerRows<C>& r)
+template <int C, int PL>
+__device__ __forceinline__ void store_moments(const StepArgs& a, const WorkerSpan& s, int ch0,
+                                              const WorkerRows<C>& r)
 {
     if (placement_of<PL>(a) != AT_WORKER) return;
-    const int lane = lane_id();
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        if (!FULL && ch >= nch) continue;
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-        st4<VEC, FULL>(mw, n, a.d, r.m[ch]);
-        st4<VEC, FULL>(vw, n, a.d, r.v[ch]);
+        st4(s.m, ch0 + ch, r.m[ch]);
+        st4(s.v, ch0 + ch, r.v[ch]);
     }
 }
 
@@ -1245,22 +1254,21 @@ struct ServerRows {
     float4 m[C], v[C], e[C], x[C];
 };
 
-template <int C, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void load_server(const StepArgs& a, int64_t base, int nch, bool with_e, bool with_x,
+template <int C, int PL>
+__device__ __forceinline__ void load_server(const StepArgs& a, int64_t base, int left, bool with_e, bool with_x,
                                             ServerRows<C>& r)
 {
-    const int lane = lane_id();
+    const Row m = row_of(a.m + base, left), v = row_of(a.v + base, left);
+    const Row e = row_of(a.e_s + base, left), x = row_of(a.x + base, left);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
         r.m[ch] = r.v[ch] = r.e[ch] = r.x[ch] = zero4();
-        if (!FULL && ch >= nch) continue;
         if (placement_of<PL>(a) == AT_SERVER) {
-            r.m[ch] = ld4<VEC, FULL>(a.m, n, a.d);
-            r.v[ch] = ld4<VEC, FULL>(a.v, n, a.d);
+            r.m[ch] = ld4(m, ch);
+            r.v[ch] = ld4(v, ch);
         }
-        if (with_e) r.e[ch] = ld4<VEC, FULL>(a.e_s, n, a.d);
-        if (with_x) r.x[ch] = ld4<VEC, FULL>(a.x, n, a.d);
+        if (with_e) r.e[ch] = ld4(e, ch);
+        if (with_x) r.x[ch] = ld4(x, ch);
     }
 }
 
@@ -1272,11 +1280,10 @@ __device__ __forceinline__ float avg_of(float x, float fN, float invN, bool pow2
 }
 
 // Server input from the worker sum: Adam (at the server) or the average.
-template <int C, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void server_input(const StepArgs& a, const float4 (&acc)[C], int64_t base, int nch,
+template <int C, int PL>
+__device__ __forceinline__ void server_input(const StepArgs& a, const float4 (&acc)[C], int64_t base, int left,
                                              ServerRows<C>& sr, float4 (&u)[C])
 {
-    const int lane = lane_id();
     const float fN = (float)a.N;
     const bool pow2 = (a.N & (a.N - 1)) == 0;
     const float invN = 1.0f / fN;
@@ -1287,7 +1294,6 @@ __device__ __forceinline__ void server_input(const StepArgs& a, const float4 (&a
         avg[ch] = make_float4(avg_of(acc[ch].x, fN, invN, pow2), avg_of(acc[ch].y, fN, invN, pow2),
                               avg_of(acc[ch].z, fN, invN, pow2), avg_of(acc[ch].w, fN, invN, pow2));
     if (placement_of<PL>(a) == AT_SERVER) {
-        // the moments of every chunk (those past d are zero and unused)
         float mm[4 * C], vv[4 * C], uu[4 * C];
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) {
@@ -1309,97 +1315,105 @@ __device__ __forceinline__ void server_input(const StepArgs& a, const float4 (&a
             for (int k = 0; k < 4; ++k) set_comp(avg[ch], k, uu[4 * ch + k]);
         }
     }
+    const Row m = row_of(a.m + base, left), v = row_of(a.v + base, left);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t n = base + (int64_t)ch * kChunk + 4 * lane;
-        if (!FULL && ch >= nch) {
-            u[ch] = zero4();
-            continue;
-        }
         if (placement_of<PL>(a) == AT_SERVER) {
-            st4<VEC, FULL>(a.m, n, a.d, sr.m[ch]);
-            st4<VEC, FULL>(a.v, n, a.d, sr.v[ch]);
+            st4(m, ch, sr.m[ch]);
+            st4(v, ch, sr.v[ch]);
         }
         u[ch] = avg[ch];
     }
 }
 
-// Partial norm of a tile, reduced over the wave (one-bucket quantizers).
+// +0 past d, where the workers' dequantized values are not defined.
 template <int C>
-__device__ __forceinline__ double tile_partial(const QDev& q, const float4 (&p)[C], int64_t base, int nch,
-                                               int64_t d)
+__device__ __forceinline__ void zero_past_end(float4 (&q)[C], int left)
+{
+    if (left == C * kChunk) return;
+    ragged_only();
+#pragma unroll
+    for (int ch = 0; ch < C; ++ch)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) set_comp(q[ch], k, inside(left, ch, k) ? comp(q[ch], k) : 0.0f);
+}
+
+// Partial norm of a tile (+0 past d), reduced over the wave (one-bucket
+// quantizers).
+template <int C>
+__device__ __forceinline__ double tile_partial(const QDev& q, const float4 (&p)[C])
 {
     Partial a;
     a.sum = 0.0;
     a.mx = 0.0f;
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch)
-        if (ch < nch) partial_add4(a, q.norm, p[ch], nvalid4(base + ch * kChunk + 4 * lane_id(), d));
+    for (int ch = 0; ch < C; ++ch) partial_add4(a, q.norm, p[ch]);
     return q.norm == S_MAX ? (double)wave_max(a.mx) : wave_sum(a.sum);
 }
 
 struct TilePos {
     int64_t tile, base;
-    int nch;
+    int left;                 // elements of the tile inside d
 };
 
+// Position of tile `tile` of C chunks (`left` is 0 for one wholly past d).
+template <int C>
+__device__ __forceinline__ TilePos tile_at(const StepArgs& a, int64_t tile)
+{
+    TilePos t;
+    t.tile = tile;
+    t.base = tile * C * kChunk;
+    t.left = span_left(t.base, a.d, C * kChunk);
+    return t;
+}
+
+// The split calls' blocks: one tile per wave.
 template <int C>
 __device__ __forceinline__ bool tile_pos(const StepArgs& a, TilePos& t)
 {
-    t.tile = a.tile0 + (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x / kWave);
-    if (t.tile >= a.ntiles) return false;
-    t.base = t.tile * C * kChunk;
-    const int64_t rem = (a.d - t.base + kChunk - 1) / kChunk;
-    t.nch = rem < C ? (int)rem : C;
+    const int64_t tile = a.tile0 + (int64_t)blockIdx.x * kWavesPerBlock + wave_id();
+    if (tile >= a.ntiles) return false;
+    t = tile_at<C>(a, tile);
     return true;
 }
 
 // ---------------------------------------------------------------------------
-// One worker's share of a tile: wave w compresses worker i and leaves its
-// dequantized values in the handoff slot.
-template <int C, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void worker_load(const StepArgs& a, const TilePos& t, int i, WorkerRows<C>& r)
-{
-    const bool atw = placement_of<PL>(a) == AT_WORKER;
-    const int64_t row = (int64_t)i * a.d;
-    load_worker<C, VEC, FULL, PL>(a, a.g + row, a.e_w + row, atw ? a.m_w + row : nullptr,
-                                  atw ? a.v_w + row : nullptr, t.base, t.nch, r);
-}
-
-template <int C, bool VEC, bool FULL, class QW, int PL>
+// One worker's share of a tile (the tile that starts at chunk ch0 of the
+// block's span): compress it and leave its dequantized values in the handoff
+// slot.
+template <int C, class QW, int PL>
 __device__ __forceinline__ void worker_compute(const StepArgs& a, const TilePos& t, const float* lut_w, int i,
-                                               WorkerRows<C>& r, WordSink& sink, float4* slot)
+                                               const WorkerSpan& s, int ch0, WorkerRows<C>& r, WordSink& sink,
+                                               float4* slot)
 {
     const int lane = lane_id();
     const bool wglobal = has_scale<QW>(a.qw) && QW::cpb(a.qw) == 0;
-    const bool atw = placement_of<PL>(a) == AT_WORKER;
-    const int64_t row = (int64_t)i * a.d;
     float4 p[C], dq[C];
     if constexpr (select_first<QW, C>()) {
-        // the selection and the code words first, while the rows arrive
+        // the selection and the code words first, while the rows arrive; the
+        // rows' loads go out after the draws (issued before them, as the
+        // compiler would, the rows held registers through both: random-64 of
+        // 2048 5.31 against 5.08 ms)
         float4 none[C];
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) none[ch] = zero4();
-        const uint32_t kb = sparsify_tile<C, FULL, QW, true>(a.qw, none, t.base, t.nch, a.d, a.k0, a.k1, a.t,
-                                                             (uint32_t)i, nullptr, sink, dq);
+        const uint32_t kb = sparsify_tile<C, QW, true>(a.qw, none, t.base, t.left, a.k0, a.k1, a.t, (uint32_t)i,
+                                                       nullptr, sink, dq, [&]() {
+                                                           __builtin_amdgcn_sched_barrier(0);
+                                                           load_worker<C, PL>(a, s, ch0, r);
+                                                       });
         worker_p<C, PL>(a, r, p);
-        if (atw) store_moments<C, VEC, FULL, PL>(a, a.m_w + row, a.v_w + row, t.base, t.nch, r);
-        sparse_values<C, FULL, QW>(a.qw, p, kb, t.base, t.nch, a.d, a.wscales + (int64_t)i * a.qw.nscales, dq);
+        store_moments<C, PL>(a, s, ch0, r);
+        sparse_values<C, QW>(a.qw, p, kb, t.base, t.left, a.wscales + (int64_t)i * a.qw.nscales, dq);
     } else {
         worker_p<C, PL>(a, r, p);
-        if (atw) store_moments<C, VEC, FULL, PL>(a, a.m_w + row, a.v_w + row, t.base, t.nch, r);
+        store_moments<C, PL>(a, s, ch0, r);
         const float gs = wglobal ? a.wscales[(int64_t)i * a.qw.nscales] : 0.0f;
-        quantize_tile<C, FULL, QW>(a.qw, lut_w, p, t.base, t.nch, a.d, a.k0, a.k1, a.t, (uint32_t)i, gs,
-                                   a.wcodes + (int64_t)i * a.qw.words, a.wscales + (int64_t)i * a.qw.nscales, sink,
-                                   dq);
+        quantize_tile<C, QW>(a.qw, lut_w, p, t.base, t.left, a.k0, a.k1, a.t, (uint32_t)i, gs,
+                             a.wcodes + (int64_t)i * a.qw.words, a.wscales + (int64_t)i * a.qw.nscales, sink, dq);
     }
-    float* e = a.e_w + row;
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch) {
-        if (!FULL && ch >= t.nch) continue;
-        const int64_t n = t.base + (int64_t)ch * kChunk + 4 * lane;
-        st4<VEC, FULL>(e, n, a.d, a.qw.ef ? sub4(p[ch], dq[ch]) : zero4());
-    }
+    for (int ch = 0; ch < C; ++ch) st4(s.e, ch0 + ch, a.qw.ef ? sub4(p[ch], dq[ch]) : zero4());
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) slot[ch * kWave + lane] = dq[ch];
 }
@@ -1415,71 +1429,26 @@ __device__ __forceinline__ void gather_group(const float4* slot, int cnt, float4
     }
 }
 
-// Position of tile `tile` of C chunks.
-template <int C>
-__device__ __forceinline__ TilePos tile_at(const StepArgs& a, int64_t tile)
+// Worker i on the block's K consecutive tiles: all tiles' rows are loaded
+// first, so the later tiles' loads are in flight while the first is
+// compressed; the codes of the tiles leave through one sink, as one piece.
+// Tile k's dequantized values go to slots + (k*G + w)*C*64.
+template <int C, int K, class QW, int PL>
+__device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&tp)[K], const float* lut_w, int i,
+                                             float4* slots, int G, int w)
 {
-    TilePos t;
-    t.tile = tile;
-    t.base = tile * C * kChunk;
-    const int64_t rem = (a.d - t.base + kChunk - 1) / kChunk;
-    t.nch = rem < C ? (int)rem : C;
-    return t;
-}
-
-// Worker i's rows of the block's nt consecutive tiles.
-template <int C, int K, bool VEC, bool FULL, int PL>
-__device__ __forceinline__ void worker_rows(const StepArgs& a, const TilePos (&tp)[K], int nt, int i,
-                                            WorkerRows<C> (&r)[K])
-{
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (k < nt) worker_load<C, VEC, FULL, PL>(a, tp[k], i, r[k]);
-}
-
-// Worker i on the block's nt consecutive tiles, from rows loaded beforehand
-// (worker_rows; all tiles' rows are loaded first, so the later tiles' loads
-// are in flight while the first is compressed); the codes of the tiles leave
-// through one sink, as one piece.  Tile k's dequantized values go to
-// slots + (k*G + w)*C*64.
-template <int C, int K, bool VEC, bool FULL, class QW, int PL>
-__device__ __forceinline__ void worker_tiles(const StepArgs& a, const TilePos (&tp)[K], int nt, const float* lut_w,
-                                             int i, WorkerRows<C> (&r)[K], float4* slots, int G, int w)
-{
-    WordSink sink = message_sink<QW>(a.qw, a.wcodes + (int64_t)i * a.qw.words, tp[0].base);
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (k < nt)
-            worker_compute<C, VEC, FULL, QW, PL>(a, tp[k], lut_w, i, r[k], sink,
-                                                 slots + ((int64_t)k * G + w) * C * kWave);
-    sink.flush();
-}
-
-// Worker i on the block's tiles: its rows are loaded, then compressed.  The
-// two spellings take the same steps; the register allocator does better with
-// the first on fully specialized whole-tile kernels (BERT-sized round 94 -> 89
-// VGPRs, random-k 96 with a 24-byte spill -> 95 without) and with the second
-// on the others (the generic 8-chunk kernel spills with the first).
-template <int C, int K, bool VEC, bool FULL, class QW, int PL, bool INLINE>
-__device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&tp)[K], int nt, const float* lut_w,
-                                             int i, float4* slots, int G, int w)
-{
+    const int64_t base = tp[0].base, row = (int64_t)i * a.d;
+    const int left = span_left(base, a.d, K * C * kChunk);
+    const WorkerSpan s = worker_span<PL>(a, a.g + row, a.e_w + row, a.m_w + row, a.v_w + row, base, left);
     WorkerRows<C> r[K];
-    if constexpr (INLINE) {
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k < nt) worker_load<C, VEC, FULL, PL>(a, tp[k], i, r[k]);
-        WordSink sink = message_sink<QW>(a.qw, a.wcodes + (int64_t)i * a.qw.words, tp[0].base);
+    for (int k = 0; k < K; ++k)
+        if constexpr (!select_first<QW, C>()) load_worker<C, PL>(a, s, k * C, r[k]);
+    WordSink sink = message_sink<QW>(a.qw, a.wcodes + (int64_t)i * a.qw.words, base, left);
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (k < nt)
-                worker_compute<C, VEC, FULL, QW, PL>(a, tp[k], lut_w, i, r[k], sink,
-                                                     slots + ((int64_t)k * G + w) * C * kWave);
-        sink.flush();
-    } else {
-        worker_rows<C, K, VEC, FULL, PL>(a, tp, nt, i, r);
-        worker_tiles<C, K, VEC, FULL, QW, PL>(a, tp, nt, lut_w, i, r, slots, G, w);
-    }
+    for (int k = 0; k < K; ++k)
+        worker_compute<C, QW, PL>(a, tp[k], lut_w, i, s, k * C, r[k], sink, slots + ((int64_t)k * G + w) * C * kWave);
+    sink.flush();
 }
 
 // 8-chunk tiles whose server bucket is the whole tile (a scaled or sign
@@ -1518,33 +1487,33 @@ __device__ __forceinline__ void gather_chunk(const float4* slot, int cnt, int ch
 // of the bucket norm meet in `red` ([C][64], LDS) and every serving wave adds
 // them in chunk order (the order of the one-wave round, so the scale has the
 // same bits), then quantizes its chunk under that scale and applies it.
-// Every wave of the block takes part in both barriers.  FULL = false: a
-// ragged tile, served on the waves of its nch chunks, with bounds checks.
-template <int C, bool VEC, bool FULL, class QS, int PL>
+// Every wave of the block takes part in both barriers.
+template <int C, class QS, int PL>
 __device__ __forceinline__ void serve_split(const StepArgs& a, const TilePos& t, const float* lut_s,
                                             const float4* slots, int cnt, float4 acc, double* red)
 {
     using QG = typename GivenScale<QS>::type;
     const int lane = lane_id();
-    const int w = (int)(threadIdx.x / kWave);
-    const int nch = FULL ? C : t.nch;
-    const bool serving = w < nch;
+    const int w = wave_id();
+    const bool serving = w < C;
     const int ch = serving ? w : 0;
     const int64_t base = t.base + (int64_t)ch * kChunk;
+    const int left = span_left(base, a.d, kChunk);
     const int norm = QS::norm(a.qs);
     ServerRows<1> sr;
-    if (serving) load_server<1, VEC, FULL, PL>(a, base, 1, true, true, sr);
+    if (serving) load_server<1, PL>(a, base, left, true, true, sr);
     __syncthreads();                           // the last group's handoff is complete
     float4 u[1], q[1], dq[1];
     if (serving) {
         gather_chunk<C>(slots, cnt, ch, acc);
         const float4 s1[1] = {acc};
-        server_input<1, VEC, FULL, PL>(a, s1, base, 1, sr, u);
+        server_input<1, PL>(a, s1, base, left, sr, u);
         q[0] = add4(u[0], sr.e[0]);
+        zero_past_end<1>(q, left);
         Partial p;
         p.sum = 0.0;
         p.mx = 0.0f;
-        partial_add4(p, norm, q[0], FULL ? 4 : nvalid4(base + 4 * lane, a.d));
+        partial_add4(p, norm, q[0]);
         red[ch * kWave + lane] = norm == S_MAX ? (double)p.mx : p.sum;
     }
     __syncthreads();                           // every chunk's partial is in LDS
@@ -1553,22 +1522,19 @@ __device__ __forceinline__ void serve_split(const StepArgs& a, const TilePos& t,
     float mx = 0.0f;
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-        if (!FULL && j >= nch) continue;
         if (norm == S_MAX) mx = fmaxf(mx, (float)red[j * kWave + lane]);
         else tot += red[j * kWave + lane];
     }
     const double S = norm == S_MAX ? 0.0 : wave_sum(tot);
     const float M = norm == S_MAX ? wave_max(mx) : 0.0f;
-    const int64_t nb = FULL ? a.qs.B : ((a.d - t.base) < a.qs.B ? (a.d - t.base) : a.qs.B);
-    const float scale = scale_from(norm, S, M, nb);
+    const float scale = scale_from(norm, S, M, t.left);
     if (ch == 0 && lane == 0) a.sscales[(t.base >> 8) >> QS::cpb_shift(a.qs)] = scale;
-    WordSink sink = message_sink<QG>(a.qs, a.scodes, base);
-    quantize_tile<1, FULL, QG>(a.qs, lut_s, q, base, 1, a.d, a.k0, a.k1, a.t, kServerStream, scale, a.scodes,
-                               a.sscales, sink, dq);
+    WordSink sink = message_sink<QG>(a.qs, a.scodes, base, left);
+    quantize_tile<1, QG>(a.qs, lut_s, q, base, left, a.k0, a.k1, a.t, kServerStream, scale, a.scodes, a.sscales, sink,
+                         dq);
     sink.flush();
-    const int64_t n = base + 4 * lane;
-    st4<VEC, FULL>(a.e_s, n, a.d, a.qs.ef ? sub4(q[0], dq[0]) : zero4());
-    st4<VEC, FULL>(a.x, n, a.d, sub4(sr.x[0], dq[0]));
+    st4(row_of(a.e_s + base, left), 0, a.qs.ef ? sub4(q[0], dq[0]) : zero4());
+    st4(row_of(a.x + base, left), 0, sub4(sr.x[0], dq[0]));
 }
 
 // 8-chunk tiles with a sparsifier on the server (top-k, random-k): the
@@ -1589,59 +1555,59 @@ struct SparseServe<QCt<K, B, NM, CPB>, C> {
 // the last group, runs Adam on it and adds e_s; it leaves q and x in the
 // handoff slots of workers 0 and 1 of chunk ch, which no other wave reads.
 // Wave 0 then sparsifies the tile's q and writes e_s and x.  Every wave of
-// the block takes part in both barriers.  FULL = false: a ragged tile, with
-// bounds checks.
-template <int C, bool VEC, bool FULL, class QS, int PL>
+// the block takes part in both barriers.
+template <int C, class QS, int PL>
 __device__ __forceinline__ void serve_sparse(const StepArgs& a, const TilePos& t, const float* lut_s,
                                              float4* slots, int cnt, float4 acc)
 {
     const int lane = lane_id();
-    const int w = (int)(threadIdx.x / kWave);
-    const int nch = FULL ? C : t.nch;
-    const bool serving = w < nch;
+    const int w = wave_id();
+    const bool serving = w < C;
     const int ch = serving ? w : 0;
     const int64_t base = t.base + (int64_t)ch * kChunk;
+    const int left = span_left(base, a.d, kChunk);
     ServerRows<1> sr;
-    if (serving) load_server<1, VEC, FULL, PL>(a, base, 1, true, true, sr);
+    if (serving) load_server<1, PL>(a, base, left, true, true, sr);
     __syncthreads();                           // the last group's handoff is complete
     if (serving) {
         gather_chunk<C>(slots, cnt, ch, acc);
         const float4 s1[1] = {acc};
         float4 u[1];
-        server_input<1, VEC, FULL, PL>(a, s1, base, 1, sr, u);
-        slots[ch * kWave + lane] = add4(u[0], sr.e[0]);
+        server_input<1, PL>(a, s1, base, left, sr, u);
+        float4 qc[1] = {add4(u[0], sr.e[0])};
+        zero_past_end<1>(qc, left);
+        slots[ch * kWave + lane] = qc[0];
         slots[(C + ch) * kWave + lane] = sr.x[0];
     }
     __syncthreads();                           // q and x of every chunk are in LDS
     if (w != 0) return;
     float4 q[C], dq[C];
-    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base);
+    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base, t.left);
     if constexpr (select_first<QS, C>()) {
 #pragma unroll
         for (int j = 0; j < C; ++j) q[j] = zero4();
-        const uint32_t kb = sparsify_tile<C, FULL, QS, true>(a.qs, q, t.base, t.nch, a.d, a.k0, a.k1, a.t,
-                                                             kServerStream, nullptr, sink, dq);
+        const uint32_t kb = sparsify_tile<C, QS, true>(a.qs, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream,
+                                                       nullptr, sink, dq);
 #pragma unroll
-        for (int j = 0; j < C; ++j) q[j] = (FULL || j < nch) ? slots[j * kWave + lane] : zero4();
-        sparse_values<C, FULL, QS>(a.qs, q, kb, t.base, t.nch, a.d, a.sscales, dq);
+        for (int j = 0; j < C; ++j) q[j] = slots[j * kWave + lane];
+        sparse_values<C, QS>(a.qs, q, kb, t.base, t.left, a.sscales, dq);
     } else {
 #pragma unroll
-        for (int j = 0; j < C; ++j) q[j] = (FULL || j < nch) ? slots[j * kWave + lane] : zero4();
-        quantize_tile<C, FULL, QS>(a.qs, lut_s, q, t.base, t.nch, a.d, a.k0, a.k1, a.t, kServerStream, 0.0f,
-                                   a.scodes, a.sscales, sink, dq);
+        for (int j = 0; j < C; ++j) q[j] = slots[j * kWave + lane];
+        quantize_tile<C, QS>(a.qs, lut_s, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream, 0.0f, a.scodes,
+                             a.sscales, sink, dq);
     }
     sink.flush();
+    const Row e = row_of(a.e_s + t.base, t.left), x = row_of(a.x + t.base, t.left);
 #pragma unroll
     for (int j = 0; j < C; ++j) {
-        if (!FULL && j >= nch) continue;
-        const int64_t n = t.base + (int64_t)j * kChunk + 4 * lane;
-        st4<VEC, FULL>(a.e_s, n, a.d, a.qs.ef ? sub4(q[j], dq[j]) : zero4());
-        st4<VEC, FULL>(a.x, n, a.d, sub4(slots[(C + j) * kWave + lane], dq[j]));
+        st4(e, j, a.qs.ef ? sub4(q[j], dq[j]) : zero4());
+        st4(x, j, sub4(slots[(C + j) * kWave + lane], dq[j]));
     }
 }
 
 // ---------------------------------------------------------------------------
-// The fused round on nt <= K consecutive tiles per block.  The block has
+// The fused round on K consecutive tiles per block.  The block has
 // G = min(N, 16) waves.  Workers are taken in groups of G: wave w compresses
 // worker g0 + w on every tile of the block and hands its dequantized values
 // over through LDS.  Wave k then serves tile k: it adds the handoffs in
@@ -1657,25 +1623,23 @@ __device__ __forceinline__ void serve_sparse(const StepArgs& a, const TilePos& t
 // the wait for the workers, without the loaded rows being live during the
 // earlier groups.
 // ---------------------------------------------------------------------------
-template <int C, int K, bool VEC, bool FULL, class QW, class QS, int PL>
-__device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, int nt, const float* lut_w,
-                                            const float* lut_s, float4* xfer, int G, double* red)
+template <int C, int K, class QW, class QS, int PL>
+__device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, const float* lut_w, const float* lut_s,
+                                            float4* xfer, int G, double* red)
 {
     const int lane = lane_id();
-    const int w = (int)(threadIdx.x / kWave);
+    const int w = wave_id();
     const bool sglobal = has_scale<QS>(a.qs) && QS::cpb(a.qs) == 0;
     // The server side on C waves, one chunk each (the launch gives the block
     // at least C waves); otherwise wave k serves tile k.
     constexpr bool kSparse = SparseServe<QS, C>::value && K == 1;
     constexpr bool kSplit = (SplitServe<QS, C>::value || kSparse) && K == 1;
-    // Whole-tile launches give every block exactly K tiles.  With that known
-    // at compile time, each wave's loads of all K tiles and its work on them
-    // are straight-line code, so the compiler waits for each tile's rows
-    // only before that tile's arithmetic.  (With the later tiles under a
+    // Every block works on exactly K tiles; those past the last one have no
+    // elements inside d.  So each wave's loads of all K tiles and its work on
+    // them are straight-line code, and the compiler waits for each tile's
+    // rows only before that tile's arithmetic.  (With the later tiles under a
     // branch it waited for every load, and for the stores issued since,
     // before the first tile and again before the second.)
-    if constexpr (FULL) nt = K;
-
     TilePos tp[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) tp[k] = tile_at<C>(a, tile0 + k);
@@ -1688,7 +1652,7 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, in
         if constexpr (kSplit) {
             if (w < C) gather_chunk<C>(grp, cnt, w, acc[0]);
         } else {
-            if (w < nt) gather_group<C>(grp + (int64_t)w * G * C * kWave, cnt, acc);
+            if (w < K) gather_group<C>(grp + (int64_t)w * G * C * kWave, cnt, acc);
         }
     };
 
@@ -1700,50 +1664,49 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, in
     const int64_t per_buf = (int64_t)K * G * C * kWave;
     int buf = 0, g0 = 0;
     float4* slots;
-    constexpr bool kInline = FULL && QW::fixed && QS::fixed;
     for (; g0 + G < a.N; g0 += G, buf ^= a.one_buffer ? 0 : 1) {
         slots = xfer + buf * per_buf;
-        worker_round<C, K, VEC, FULL, QW, PL, kInline>(a, tp, nt, lut_w, g0 + w, slots, G, w);
+        worker_round<C, K, QW, PL>(a, tp, lut_w, g0 + w, slots, G, w);
         __syncthreads();
         gather(slots, G);
         if (a.one_buffer) __syncthreads();
     }
     slots = xfer + buf * per_buf;
-    if (g0 + w < a.N) worker_round<C, K, VEC, FULL, QW, PL, kInline>(a, tp, nt, lut_w, g0 + w, slots, G, w);
+    if (g0 + w < a.N) worker_round<C, K, QW, PL>(a, tp, lut_w, g0 + w, slots, G, w);
     if constexpr (kSplit) {
-        if constexpr (kSparse) serve_sparse<C, VEC, FULL, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0]);
-        else serve_split<C, VEC, FULL, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0], red);
+        if constexpr (kSparse) serve_sparse<C, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0]);
+        else serve_split<C, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0], red);
         return;
     } else {
-    const TilePos t = tile_at<C>(a, tile0 + (w < nt ? w : 0));
+    const TilePos t = tile_at<C>(a, tile0 + (w < K ? w : 0));
     ServerRows<C> sr;
-    if (w < nt) load_server<C, VEC, FULL, PL>(a, t.base, t.nch, true, !sglobal, sr);
+    if (w < K) load_server<C, PL>(a, t.base, t.left, true, !sglobal, sr);
     __syncthreads();
-    if (w >= nt) return;
+    if (w >= K || t.left == 0) return;
     gather_group<C>(slots + (int64_t)w * G * C * kWave, a.N - g0, acc);
 
     float4 u[C], q[C], dq[C];
-    server_input<C, VEC, FULL, PL>(a, acc, t.base, t.nch, sr, u);
+    server_input<C, PL>(a, acc, t.base, t.left, sr, u);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) q[ch] = add4(u[ch], sr.e[ch]);
+    zero_past_end<C>(q, t.left);
     if (sglobal) {
+        const Row ub = row_of(a.ubuf + t.base, t.left);
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch)
-            if (FULL || ch < t.nch) st4<VEC, FULL>(a.ubuf, t.base + (int64_t)ch * kChunk + 4 * lane, a.d, u[ch]);
-        const double part = tile_partial<C>(a.qs, q, t.base, t.nch, a.d);
+        for (int ch = 0; ch < C; ++ch) st4(ub, ch, u[ch]);
+        const double part = tile_partial<C>(a.qs, q);
         if (lane == 0) a.spart[t.tile] = part;
         return;
     }
-    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base);
-    quantize_tile<C, FULL, QS>(a.qs, lut_s, q, t.base, t.nch, a.d, a.k0, a.k1, a.t, kServerStream, 0.0f, a.scodes,
-                               a.sscales, sink, dq);
+    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base, t.left);
+    quantize_tile<C, QS>(a.qs, lut_s, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream, 0.0f, a.scodes, a.sscales,
+                         sink, dq);
     sink.flush();
+    const Row e = row_of(a.e_s + t.base, t.left), x = row_of(a.x + t.base, t.left);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        if (!FULL && ch >= t.nch) continue;
-        const int64_t n = t.base + (int64_t)ch * kChunk + 4 * lane;
-        st4<VEC, FULL>(a.e_s, n, a.d, a.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
-        st4<VEC, FULL>(a.x, n, a.d, sub4(sr.x[ch], dq[ch]));
+        st4(e, ch, a.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
+        st4(x, ch, sub4(sr.x[ch], dq[ch]));
     }
     }
 }
@@ -1756,7 +1719,7 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, in
 // point at that worker's d-vectors; a.wcodes/a.wscales at its message).
 // Blocks of 4 independent waves, one tile each; QW fixes the worker
 // quantizer at compile time (by default it is read at run time).
-template <int C, bool VEC, class QW = QRt>
+template <int C, class QW = QRt>
 __global__ __launch_bounds__(kBlock) void worker_kernel(StepArgs a)
 {
     __shared__ float lut_w[kLutSize];
@@ -1764,24 +1727,20 @@ __global__ __launch_bounds__(kBlock) void worker_kernel(StepArgs a)
     __syncthreads();
     TilePos t;
     if (!tile_pos<C>(a, t)) return;
-    const int lane = lane_id();
     const bool wglobal = has_scale<QW>(a.qw) && QW::cpb(a.qw) == 0;
-    const bool atw = a.placement == AT_WORKER;
+    const WorkerSpan s = worker_span<-1>(a, a.g, a.e_w, a.m_w, a.v_w, t.base, t.left);
     WorkerRows<C> r;
     float4 p[C], dq[C];
-    load_worker<C, VEC, false, -1>(a, a.g, a.e_w, a.m_w, a.v_w, t.base, t.nch, r);
+    load_worker<C, -1>(a, s, 0, r);
     worker_p<C, -1>(a, r, p);
-    if (atw) store_moments<C, VEC, false, -1>(a, a.m_w, a.v_w, t.base, t.nch, r);
+    store_moments<C, -1>(a, s, 0, r);
     const float gs = wglobal ? a.wscales[0] : 0.0f;
-    WordSink sink = message_sink<QW>(a.qw, a.wcodes, t.base);
-    quantize_tile<C, false, QW>(a.qw, lut_w, p, t.base, t.nch, a.d, a.k0, a.k1, a.t, (uint32_t)a.worker, gs,
-                                 a.wcodes, a.wscales, sink, dq);
+    WordSink sink = message_sink<QW>(a.qw, a.wcodes, t.base, t.left);
+    quantize_tile<C, QW>(a.qw, lut_w, p, t.base, t.left, a.k0, a.k1, a.t, (uint32_t)a.worker, gs, a.wcodes, a.wscales,
+                         sink, dq);
     sink.flush();
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch) {
-        if (ch >= t.nch) continue;
-        st4<VEC>(a.e_w, t.base + (int64_t)ch * kChunk + 4 * lane, a.d, a.qw.ef ? sub4(p[ch], dq[ch]) : zero4());
-    }
+    for (int ch = 0; ch < C; ++ch) st4(s.e, ch, a.qw.ef ? sub4(p[ch], dq[ch]) : zero4());
 }
 
 // Whether the aggregate decodes worker messages through a per-wave code
@@ -1801,12 +1760,10 @@ __host__ __device__ constexpr bool kScaledTable()
 }
 
 // Split call: dequantize the N worker messages, average in ascending worker
-// order, run Adam at the server if placed there; result in a.ubuf.  FULL:
-// every tile of the launch lies wholly inside d (no per-tile checks).
-template <int C, bool VEC, class QW = QRt, bool FULL = false>
+// order, run Adam at the server if placed there; result in a.ubuf.
+template <int C, class QW = QRt>
 __global__ __launch_bounds__(kBlock) void aggregate_kernel(StepArgs a)
 {
-    static_assert(!FULL || VEC, "whole-tile kernels need aligned rows");
     __shared__ float lut_w[kLutSize];
     __shared__ __attribute__((aligned(16))) uint32_t stage_all[kWavesPerBlock][stage_words<C, QW>()];
     __shared__ float stab_all[kScaledTable<QW, C>() ? kWavesPerBlock : 1][kWave];
@@ -1814,9 +1771,7 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(StepArgs a)
     __syncthreads();
     TilePos t;
     if (!tile_pos<C>(a, t)) return;
-    const int nch = FULL ? C : t.nch;
-    uint32_t* stage = stage_all[threadIdx.x / kWave];
-    const int lane = lane_id();
+    uint32_t* stage = stage_all[wave_id()];
     float4 acc[C], dq[C], u[C];
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) acc[ch] = zero4();
@@ -1826,15 +1781,15 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(StepArgs a)
     // set copied forward each step, the copy waited for the load at once).
     const bool planes = plane_coded<QW>(a.qw);
     if (planes) {
+        const int stab_row = kScaledTable<QW, C>() ? wave_id() : 0;
         CodeWords<C, QW> wv0, wv1;
         float sc0[C], sc1[C];
         const auto load = [&](int64_t i, CodeWords<C, QW>& wv, float (&sc)[C]) {
-            load_code_words<C, QW>(a.qw, a.wcodes + i * a.qw.words, t.base, nch, wv);
-            load_chunk_scales<C, QW>(a.qw, a.wscales + i * a.qw.nscales, t.base, nch, sc);
+            load_code_words<C, QW>(a.qw, a.wcodes + i * a.qw.words, t.base, t.left, wv);
+            load_chunk_scales<C, QW>(a.qw, a.wscales + i * a.qw.nscales, t.base, t.left, sc);
         };
         const auto add = [&](const CodeWords<C, QW>& wv, const float (&sc)[C]) {
-            decode_words<C, QW, true, kScaledTable<QW, C>()>(a.qw, lut_w, wv, sc, t.base, nch, a.d, stage, dq,
-                                                              stab_all[threadIdx.x / kWave]);
+            decode_words<C, QW, true, kScaledTable<QW, C>()>(a.qw, lut_w, wv, sc, stage, dq, stab_all[stab_row]);
 #pragma unroll
             for (int ch = 0; ch < C; ++ch) acc[ch] = add4(acc[ch], dq[ch]);
         };
@@ -1850,7 +1805,7 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(StepArgs a)
     } else {
         for (int i = 0; i < a.N; ++i) {
             dequant_tile<C, QW>(a.qw, lut_w, a.wcodes + (int64_t)i * a.qw.words,
-                                 a.wscales + (int64_t)i * a.qw.nscales, t.base, nch, a.d, stage, dq);
+                                 a.wscales + (int64_t)i * a.qw.nscales, t.base, t.left, stage, dq);
 #pragma unroll
             for (int ch = 0; ch < C; ++ch) acc[ch] = add4(acc[ch], dq[ch]);
         }
@@ -1858,17 +1813,17 @@ __global__ __launch_bounds__(kBlock) void aggregate_kernel(StepArgs a)
     // The server's rows load after the decoding: held through it, they cost
     // occupancy (BERT-sized 4-bit, 16 workers: 843 -> 817 us).
     ServerRows<C> sr;
-    load_server<C, VEC, FULL, -1>(a, t.base, nch, false, false, sr);
-    server_input<C, VEC, FULL, -1>(a, acc, t.base, nch, sr, u);
+    load_server<C, -1>(a, t.base, t.left, false, false, sr);
+    server_input<C, -1>(a, acc, t.base, t.left, sr, u);
+    const Row ub = row_of(a.ubuf + t.base, t.left);
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch)
-        if (FULL || ch < nch) st4<VEC, FULL>(a.ubuf, t.base + (int64_t)ch * kChunk + 4 * lane, a.d, u[ch]);
+    for (int ch = 0; ch < C; ++ch) st4(ub, ch, u[ch]);
 }
 
 
 // Split call: the server's compression of u (a.ubuf) plus e_s; with a.apply
 // also x -= its message.  QS: the server quantizer's traits.
-template <int C, bool VEC, class QS = QRt>
+template <int C, class QS = QRt>
 __global__ __launch_bounds__(kBlock) void server_kernel(StepArgs args)
 {
     const StepArgs a = with_step(args);
@@ -1877,32 +1832,26 @@ __global__ __launch_bounds__(kBlock) void server_kernel(StepArgs args)
     __syncthreads();
     TilePos t;
     if (!tile_pos<C>(a, t)) return;
-    const int lane = lane_id();
     const bool sglobal = has_scale<QS>(a.qs) && QS::cpb(a.qs) == 0;
+    const Row u = row_of(a.ubuf + t.base, t.left), e = row_of(a.e_s + t.base, t.left);
+    const Row x = row_of(a.x + t.base, t.left);
     float4 q[C], dq[C];
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch) {
-        q[ch] = zero4();
-        if (ch >= t.nch) continue;
-        const int64_t n = t.base + (int64_t)ch * kChunk + 4 * lane;
-        q[ch] = add4(ld4<VEC>(a.ubuf, n, a.d), ld4<VEC>(a.e_s, n, a.d));
-    }
+    for (int ch = 0; ch < C; ++ch) q[ch] = add4(ld4(u, ch), ld4(e, ch));
     const float gs = sglobal ? a.sscales[0] : 0.0f;
-    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base);
-    quantize_tile<C, false, QS>(a.qs, lut_s, q, t.base, t.nch, a.d, a.k0, a.k1, a.t, kServerStream, gs, a.scodes,
-                                a.sscales, sink, dq);
+    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base, t.left);
+    quantize_tile<C, QS>(a.qs, lut_s, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream, gs, a.scodes, a.sscales, sink,
+                         dq);
     sink.flush();
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        if (ch >= t.nch) continue;
-        const int64_t n = t.base + (int64_t)ch * kChunk + 4 * lane;
-        st4<VEC>(a.e_s, n, a.d, a.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
-        if (a.apply) st4<VEC>(a.x, n, a.d, sub4(ld4<VEC>(a.x, n, a.d), dq[ch]));
+        st4(e, ch, a.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
+        if (a.apply) st4(x, ch, sub4(ld4(x, ch), dq[ch]));
     }
 }
 
 // Split call: x -= the dequantized server message.
-template <int C, bool VEC, class QS = QRt>
+template <int C, class QS = QRt>
 __global__ __launch_bounds__(kBlock) void apply_kernel(StepArgs a)
 {
     __shared__ float lut_s[kLutSize];
@@ -1911,15 +1860,11 @@ __global__ __launch_bounds__(kBlock) void apply_kernel(StepArgs a)
     __syncthreads();
     TilePos t;
     if (!tile_pos<C>(a, t)) return;
-    const int lane = lane_id();
+    const Row x = row_of(a.x + t.base, t.left);
     float4 dq[C];
-    dequant_tile<C, QS>(a.qs, lut_s, a.scodes, a.sscales, t.base, t.nch, a.d, stage_all[threadIdx.x / kWave], dq);
+    dequant_tile<C, QS>(a.qs, lut_s, a.scodes, a.sscales, t.base, t.left, stage_all[wave_id()], dq);
 #pragma unroll
-    for (int ch = 0; ch < C; ++ch) {
-        if (ch >= t.nch) continue;
-        const int64_t n = t.base + (int64_t)ch * kChunk + 4 * lane;
-        st4<VEC>(a.x, n, a.d, sub4(ld4<VEC>(a.x, n, a.d), dq[ch]));
-    }
+    for (int ch = 0; ch < C; ++ch) st4(x, ch, sub4(ld4(x, ch), dq[ch]));
 }
 
 // Floats of the code-table region of a fused-round block with G waves: room
@@ -1999,23 +1944,28 @@ __device__ __forceinline__ int64_t block_slot(const StepArgs& a)
 // MW > 0 overrides the minimum waves per SIMD of the launch bounds (the
 // register cap).
 //
-// FULL kernels (rows 16-byte aligned) take the tiles that lie wholly inside d
-// and carry no bounds checks; the others take any tile.  A launch covers
-// tiles [a.tile0, a.tile1); block b works on the K tiles from
-// a.tile0 + b*K.
-template <int C, bool VEC, bool FULL, class QW, class QS, int PL, int MW = 0>
+// Block b of a launch works on the K tiles from a.tile0 + b*K.  It takes every
+// tile of the round, the ragged last one included, on rows of any 4-byte
+// alignment (Row).  Bound by HBM where the round is large (BERT-sized, 16
+// workers: 5.7-5.9 TB/s, as much as a plain e += g moves), by launch and
+// memory latency where it is small.  Against separate kernels for whole tiles
+// of aligned rows and for everything else: 25,557,031 parameters (odd), 8
+// workers, stochastic 4-bit 1723 -> 605 us (1.97 -> 5.6 TB/s); 2,762,241
+// parameters, 8 workers, one bucket 298 -> 162 us; 1,049,627 parameters, 32
+// workers, sign 439 -> 94 us; 6,624 parameters, 8 workers, without
+// compression 44 -> 9.7 us (one launch instead of two with a fork and a join);
+// aligned rounds of 11M parameters and more within 1%.
+template <int C, class QW, class QS, int PL, int MW = 0>
 __global__ __launch_bounds__(max_round_waves(C) * kWave,
-                             MW > 0 ? MW : round_min_waves(C, FULL && PL == AT_SERVER)) void step_kernel(
-    StepArgs args)
+                             MW > 0 ? MW : round_min_waves(C, PL == AT_SERVER)) void step_kernel(StepArgs args)
 {
     const StepArgs a = with_step(args);
-    static_assert(!FULL || VEC, "whole-tile kernels need aligned rows");
     extern __shared__ float4 smem[];
     const int G = (int)(blockDim.x / kWave);
     float* lut_w;
     float* lut_s;
     if constexpr (WaveTable<QW>::value && WaveTable<QS>::value) {
-        float* tab = reinterpret_cast<float*>(smem) + (threadIdx.x / kWave) * 2 * kWave;
+        float* tab = reinterpret_cast<float*>(smem) + wave_id() * 2 * kWave;
         fill_wave_table<QW>(a.qw, tab);
         fill_wave_table<QS>(a.qs, tab + kWave);
         lut_w = tab;
@@ -2028,11 +1978,9 @@ __global__ __launch_bounds__(max_round_waves(C) * kWave,
         __syncthreads();
     }
     float4* xfer = smem + table_floats(G) / 4;
-    constexpr int K = kernel_tiles(C, FULL, PL, half_kernel<QW, QS, PL>());
+    constexpr int K = kernel_tiles(C, PL, half_kernel<QW, QS, PL>());
     __shared__ double red[SplitServe<QS, C>::value && K == 1 ? C * kWave : 1];
-    const int64_t first = a.tile0 + block_slot(a) * K;
-    const int64_t left = a.tile1 - first;
-    round_tiles<C, K, VEC, FULL, QW, QS, PL>(a, first, left < K ? (int)left : K, lut_w, lut_s, xfer, G, red);
+    round_tiles<C, K, QW, QS, PL>(a, a.tile0 + block_slot(a) * K, lut_w, lut_s, xfer, G, red);
 }
 
 }  // namespace

@@ -29,8 +29,7 @@ template <class Q, int MW = EA_SYM_C8_MIN_WAVES>
 constexpr SymKernel sym()
 {
     return SymKernel{8, Q::kind(QDev{}), Q::bits(QDev{}), Q::norm(QDev{}), Q::cpb(QDev{}),
-                     step_kernel<8, true, true, Q, Q, AT_SERVER, MW>,
-                     round_tiles_per_block(8, true), step_kernel<8, true, false, Q, Q, AT_SERVER, EA_SYM_C8_MIN_WAVES>};
+                     step_kernel<8, Q, Q, AT_SERVER, MW>, round_tiles_per_block(8, true)};
 }
 
 const SymKernel kSym[] = {
