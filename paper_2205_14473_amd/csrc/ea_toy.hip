@@ -5,63 +5,76 @@
 //
 // Two launches for both entry points:
 //   1. residual: res[k] = (A x)[k] - x*[k], one wave per row of A (it also
-//      clears the counters of the second launch);
-//   2. toy_round_kernel: block (b, r) owns columns [64b, 64b+64), one per
-//      lane, and the r-th of the splits of the rows of A.  Its 16 waves stage
-//      r - xi_i for a tile of rows of every worker in LDS and accumulate all
-//      workers' column sums (and the noise-free one) over contiguous row
-//      ranges, in binary64 with fused multiply-adds; the 16 partial sums of
-//      an output are added in wave order.  With several splits each block
-//      publishes its sums, and the last block of the column group to arrive
-//      adds the splits' sums in split order and goes on alone (no block
-//      waits for another); a small problem thereby spreads over many CUs
-//      instead of one block walking every row.  The last column group to
-//      finish adds the groups' partial squared norms of the noise-free
-//      gradient (lane l those of groups l, l+64, ..., then the wave's sum).
+//      clears the counter of the second launch);
+//   2. toy_round_kernel: a block owns 32 or 64 columns and all rows of A.  The sums
+//      of all workers (and the noise-free one) over the rows are one matrix
+//      product, (r - xi_i)^T A, and run on the f64 matrix cores
+//      (v_mfma_f64_16x16x4: 16 outputs x 16 columns x 4 rows), operands
+//      straight from global memory into registers: each of the 16 waves takes
+//      every 16th group of 16 rows, and the 16 partial sums of an output are
+//      added in wave order through LDS.  The last block to finish adds the
+//      blocks' partial squared norms of the noise-free gradient (lane l those
+//      of blocks l, l+64, ..., then the wave's sum); no block waits.
 //
 // ea_toy_grad writes the gradients and stops there.  ea_toy_step fuses the
 // producer into the round (quantizers without scales: Example 2, full
-// precision): wave i holds worker i's gradient for the block's columns and
-// runs its side of the round (Adam at the worker, the code, the residual);
-// its codes fill a 16-bit slice of each message word (the block's 64
-// elements are 16 lanes of one 256-element chunk).  The last wave adds the
+// precision): half a wave (a wave with 64 columns) holds worker i's gradient
+// for the block's columns and runs its side of the round (Adam at the worker,
+// the code, the residual); its codes fill an 8-bit (16-bit) slice of each
+// message word (the block's columns are 8 or 16 lanes of one 256-element
+// chunk).  The last wave adds the
 // workers' dequantized values in ascending order and runs the server side.
 // The gradient is not written to HBM unless asked for (g_out).  Both entry
 // points sum in the same order, so their gradients agree bit for bit.
 #include "ea_launch.hpp"
+
+#include <type_traits>
 
 namespace ea {
 
 namespace {
 
 constexpr int kResWaves = 4;                    // rows per residual block
+constexpr int kResAhead = 4;                    // chunks of a row loaded together
 
+// A descriptor over at most the next 2 GiB of a larger array (bytes: what is
+// left of it).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const void* p, int64_t bytes)
+{
+    const int64_t cap = 0x7FFFFFF0;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(bytes < cap ? bytes : cap), kRawBuffer);
+}
+
+// Bound by the read of A (d = 8192: 6.4 TB/s); at d = 500 by one memory
+// latency, so the loads of up to four 256-element chunks of the row go out
+// together.  A product of two binary32 values is exact in binary64.
 __global__ __launch_bounds__(kResWaves * kWave) void toy_residual_kernel(int64_t d, const float* __restrict__ A,
                                                                          const float* __restrict__ xs,
                                                                          const float* __restrict__ x,
                                                                          double* __restrict__ res,
-                                                                         uint32_t* __restrict__ counter,
-                                                                         int32_t ncounter)
+                                                                         uint32_t* __restrict__ counter)
 {
-    if (counter != nullptr && blockIdx.x == 0)
-        for (int i = (int)threadIdx.x; i < ncounter; i += (int)blockDim.x) counter[i] = 0u;
-    const int64_t k = (int64_t)blockIdx.x * kResWaves + threadIdx.x / kWave;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
+    const int64_t k = (int64_t)blockIdx.x * kResWaves + wave_id();
     if (k >= d) return;
-    const int lane = lane_id();
-    const float* row = A + k * d;
-    double s = 0.0;
-    int64_t j = lane;
-    for (; j + 3 * kWave < d; j += 4 * kWave) {
-        const float a0 = row[j], a1 = row[j + kWave], a2 = row[j + 2 * kWave], a3 = row[j + 3 * kWave];
-        const float x0 = x[j], x1 = x[j + kWave], x2 = x[j + 2 * kWave], x3 = x[j + 3 * kWave];
-        s += (double)a0 * (double)x0;
-        s += (double)a1 * (double)x1;
-        s += (double)a2 * (double)x2;
-        s += (double)a3 * (double)x3;
+    const __amdgpu_buffer_rsrc_t row = window(A + k * d, d * 4), xr = window(x, d * 4);
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < (int)d; j += kResAhead * kChunk) {
+        ea_u4v av[kResAhead], xv[kResAhead];
+#pragma unroll
+        for (int u = 0; u < kResAhead; ++u) {
+            const int off = (j + u * kChunk) * 4 + lane_id() * 16;     // past the row's end: zeros
+            av[u] = __builtin_amdgcn_raw_buffer_load_b128(row, off, 0, 0);
+            xv[u] = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < kResAhead; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                s[c] = fma((double)__uint_as_float(av[u][c]), (double)__uint_as_float(xv[u][c]), s[c]);
     }
-    for (; j < d; j += kWave) s += (double)row[j] * (double)x[j];
-    s = wave_sum(s);
-    if (lane == 0) res[k] = s - (double)xs[k];
+    const double sum = wave_sum((s[0] + s[1]) + (s[2] + s[3]));
+    if (lane_id() == 0) res[k] = sum - (double)xs[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -70,38 +83,16 @@ __global__ __launch_bounds__(kResWaves * kWave) void toy_residual_kernel(int64_t
 constexpr int kTRWaves = 16;                   // waves per block
 constexpr int kTROut = 16;                     // column sums per pass: workers + the noise-free one
 constexpr int kTRWorkers = kTROut - 1;         // workers per pass
-constexpr int kTRRows = 256;                   // rows of A per staged tile, one split
-constexpr int kTRSplitRows = 64;               // the same with several splits: one slot per thread
-constexpr int kTRMaxSplits = 8;                // splits of the rows per column group
-constexpr int kTRSplitBlocks = 1024;           // column groups x splits aimed at
+constexpr int kTRRows = 16;                    // rows per group: four matrix instructions deep
+typedef double ea_d4v __attribute__((ext_vector_type(4)));
 
-// Splits of the rows of A for d columns when the workers fit one pass (one
-// when the column groups alone fill the GPU), each a whole number of
-// kTRSplitRows tiles; `rows` receives the rows per split.
-int toy_splits(int64_t d, int64_t* rows)
+// Bits 0, 4, 8, ..., 28 of x gathered into bits 0..7.
+__device__ __forceinline__ uint32_t every_fourth_bit(uint32_t x)
 {
-    const int64_t nblk = (d + kWave - 1) / kWave;
-    int64_t R = (d + kTRSplitRows - 1) / kTRSplitRows;
-    if (R > kTRMaxSplits) R = kTRMaxSplits;
-    if (R > kTRSplitBlocks / nblk) R = kTRSplitBlocks / nblk;
-    if (R < 2) {
-        *rows = d;
-        return 1;
-    }
-    const int64_t per = (d + R - 1) / R;
-    *rows = (per + kTRSplitRows - 1) / kTRSplitRows * kTRSplitRows;
-    return (int)((d + *rows - 1) / *rows);
-}
-
-// Bits 0, 4, 8, ..., 60 of x gathered into bits 0..15.
-__device__ __forceinline__ uint32_t every_fourth_bit(uint64_t x)
-{
-    x &= 0x1111111111111111ull;
-    x = (x | (x >> 3)) & 0x0303030303030303ull;
-    x = (x | (x >> 6)) & 0x000F000F000F000Full;
-    x = (x | (x >> 12)) & 0x000000FF000000FFull;
-    x = (x | (x >> 24)) & 0x000000000000FFFFull;
-    return (uint32_t)x;
+    x &= 0x11111111u;
+    x = (x | (x >> 3)) & 0x03030303u;
+    x = (x | (x >> 6)) & 0x000F000Fu;
+    return (x | (x >> 12)) & 0x000000FFu;
 }
 
 // Code and dequantized value of one element for a quantizer without scales.
@@ -116,33 +107,43 @@ __device__ __forceinline__ void toy_code(const QDev& q, float p, uint32_t& code,
     }
 }
 
-// The block's 64 elements are lanes l0..l0+15 of chunk `chunk`, all four
-// slots.  Bit plane p of slot s is a 16-bit slice (bits l0..l0+15) of message
-// word (4 chunk + s) b + p; lane s b + p stores it.  Raw values (b = 32) are
-// stored as the binary32 element itself.
-__device__ __forceinline__ void toy_store_codes(const QDev& q, uint64_t* __restrict__ msg, int64_t col, bool in,
-                                                uint32_t code)
+// The block's COLS columns are lanes l0..l0+COLS/4-1 of a chunk, all four
+// slots.  With 32 columns each half of the wave holds them for one message
+// (msg may be null: nothing to store for that half); with 64 the wave holds
+// one message's.  Bit plane p of slot s is a slice of COLS/4 bits (whole
+// bytes) of message word (4 chunk + s) b + p; lane s b + p of the half or wave
+// stores it.  Raw values (b = 32) are stored as the binary32 element itself.
+// The last column block clears the rest of its chunk's words.
+template <int COLS>
+__device__ __forceinline__ void toy_store_codes(const QDev& q, uint64_t* __restrict__ msg, int64_t c0, bool in,
+                                                bool last, uint32_t code)
 {
-    const int lane = lane_id();
+    using Slice = std::conditional_t<COLS == 32, uint8_t, uint16_t>;
+    const int hl = lane_id() & (COLS - 1);
     if (q.kind == Q_NONE) {
-        if (in) reinterpret_cast<uint32_t*>(msg)[col] = code;
+        if (msg != nullptr && in) reinterpret_cast<uint32_t*>(msg)[c0 + hl] = code;
         return;
     }
     const int b = q.bits;
-    const int64_t c0 = col - lane;                 // first column of the block (a multiple of 64)
-    const int64_t chunk = c0 >> 8;
-    const int l0 = (int)((c0 >> 2) & 63);          // 0, 16, 32 or 48
-    uint32_t piece = 0;
-    for (int s = 0; s < 4; ++s)
-        for (int p = 0; p < b; ++p) {
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in && ((code >> p) & 1u) != 0u);
-            const uint32_t v = every_fourth_bit(m >> s);
-            piece = (uint32_t)ea_writelane_i32((int)v, s * b + p, (int)piece);
+    constexpr int kSlices = kChunk / COLS;                     // slices of a word
+    const int at = (int)(c0 / COLS) & (kSlices - 1);
+    Slice* words = reinterpret_cast<Slice*>(msg + (c0 >> 8) * 4 * b) + at;
+    for (int first = 0; first < 4 * b; first += COLS) {        // twice for 9-bit codes on 32 columns
+        const int j = first + hl;
+        const int s = (j >= b ? 1 : 0) + (j >= 2 * b ? 1 : 0) + (j >= 3 * b ? 1 : 0);
+        const int p = j - s * b;
+        uint32_t lo = 0u, hi = 0u;                             // the plane's bits of columns 0-31 and 32-63
+        for (int pl = 0; pl < b; ++pl) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in && ((code >> pl) & 1u) != 0u);
+            const bool upper = COLS == 32 && lane_id() >= 32;
+            lo = pl == p ? (upper ? (uint32_t)(m >> 32) : (uint32_t)m) : lo;
+            if (COLS == 64) hi = pl == p ? (uint32_t)(m >> 32) : hi;
         }
-    if (lane < 4 * b) {
-        const int s = lane / b, p = lane % b;
-        uint16_t* w = reinterpret_cast<uint16_t*>(msg + (4 * chunk + s) * b + p);
-        w[l0 >> 4] = (uint16_t)piece;
+        if (msg != nullptr && j < 4 * b) {
+            words[j * kSlices] = (Slice)(every_fourth_bit(lo >> s) | (COLS == 64 ? every_fourth_bit(hi >> s) << 8 : 0u));
+            if (last)
+                for (int r = 1; r < kSlices - at; ++r) words[j * kSlices + r] = 0;
+        }
     }
 }
 
@@ -157,200 +158,220 @@ struct ToyArgs {
     float *x, *e_w, *m_w, *v_w, *m, *v, *e_s;
     uint64_t *wcodes, *scodes;
     double* part;           // [blocks] partial squared norms of the noise-free gradient
-    uint32_t* counter;      // [1 + blocks]: column groups done, then each group's splits
-                            // arrived (cleared by the residual launch)
-    int32_t splits;         // splits of the rows (gridDim.y); above 1 only with one pass
-    int64_t split_rows;     // rows per split
-    double* psum;           // [blocks][splits][kTROut][64] the splits' column sums
+    uint32_t* counter;      // blocks done (cleared by the residual launch)
+    int32_t nblk;           // column blocks
     double* grad_sq;        // nullable
     float* g_out;           // nullable: [N][d] the workers' gradients, for checking
 };
 
 // ROUND: the round follows the gradients; without it the kernel only writes
 // the gradients to g_out (ea_toy_grad) and the norm.
-template <int ROWS, bool ROUND>
+//
+// Bound by the second read of A where it is large, by two memory latencies,
+// the reduction and the round's own chain at d = 500.  The vector form this
+// replaced read each residual as a broadcast from LDS for every 64 columns
+// (128 bytes of LDS a row and wave against 16 multiply-adds), which bound it
+// at any size, and split the rows over blocks that met through global memory;
+// a matrix operand instead holds 64 different residuals, and a block walks all
+// rows.  CT 16-column tiles a block, two or four: message slices are whole
+// bytes, and with two a row's piece is one 128-byte line.  The groups whose
+// loads are in flight are as many as paid: at two tiles two sets of one (one
+// set of three 99 us a step at d = 8192, three sets of one 94, against 92), at
+// four one set of two.  Measured, 10 workers, a whole step, before and after:
+// d = 500 22.4 -> 13.9 us, 4096 122 -> 39.6 us, 8192 334 -> 92 us (A read twice
+// 5.9 TB/s), 16384 1025 -> 394 us (5.5 TB/s), 40000 4.70 -> 2.37 ms (5.4 TB/s);
+// 20 workers (two passes) at d = 1557 103 -> 26 us.
+template <int CT, int SETS, int AHEAD, bool ROUND>
 __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
 {
-    constexpr int kPer = ROWS / kTRWaves;          // rows of a tile per wave
-    static_assert(ROWS % kTRWaves == 0 && ROWS * kTROut <= kTRWaves * kTROut * kWave, "tile shape");
-    // Staged tiles (row-major [row][output]), then the waves' partial sums.
-    __shared__ __attribute__((aligned(16))) double big[kTRWaves * kTROut * kWave];
-    __shared__ float xfer[kTRWorkers * kWave];
-    __shared__ int last_split;
+    constexpr int COLS = 16 * CT;
+    typedef float ea_fv __attribute__((ext_vector_type(CT)));
+    // the waves' partial sums: [wave][output][column]
+    __shared__ __attribute__((aligned(16))) double big[kTRWaves * kTROut * COLS];
+    __shared__ float xfer[kTRWorkers * COLS];
+    // Consecutive blocks go to the 8 XCDs in turn; each XCD takes a run of
+    // adjacent column blocks, which share lines when d is not a multiple of
+    // 32, so that a line is fetched into one L2.
+    const int per = (a.nblk + 7) / 8;
+    const int blk = ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8;
+    if (blk >= a.nblk || (int)blockIdx.x / 8 >= per) return;       // the whole block leaves
     const int lane = lane_id();
-    const int w = (int)(threadIdx.x / kWave);
+    const int w = wave_id();
     const int64_t d = a.d;
-    const int64_t col = (int64_t)blockIdx.x * kWave + lane;
-    const bool in = col < d;
-    const int64_t cc = in ? col : d - 1;
+    const int64_t c0 = (int64_t)blk * COLS;
+    const bool last = blk == a.nblk - 1;
     const bool atw = a.placement == AT_WORKER;
     constexpr int kServer = kTRWaves - 1;
-    float acc = 0.0f;                              // the server wave's sum of dequantized messages
-    // the server's rows of the block's columns (only this block writes them)
+    const bool server = w == kServer && lane < COLS;
+    const int64_t col = c0 + (lane & (COLS - 1));
+    const bool in = col < d;
+    // With 32 columns two outputs share a wave and the upper half of the block
+    // has none; with 64 wave o holds output o.
+    const auto norm_wave = [](int nw) { return COLS == 32 ? kTRWaves / 2 : nw; };
+    double norm_sq = 0.0;
+    float acc = 0.0f;                              // the server's sum of dequantized messages
     float sm = 0.0f, sv = 0.0f, se = 0.0f, sx = 0.0f;
-    if (ROUND && w == kServer && in) {
-        if (!atw) {
-            sm = a.m[col];
-            sv = a.v[col];
-        }
-        se = a.e_s[col];
-        sx = a.x[col];
-    }
+    // Operand lanes: n = lane % 16 is the output (residuals) or the columns
+    // CT n .. CT n + CT - 1 (A; column CT n + c belongs to matrix tile c),
+    // q = lane / 16 the four rows 4q..4q+3 of a group.
+    const int n16 = lane & 15, q4 = (lane >> 4) * 4;
+    int offA[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) offA[j] = (int)(((q4 + j) * d + CT * n16) * 4);
+    const __amdgpu_buffer_rsrc_t rres = window(a.res, d * 8), rxi = window(a.xi, (int64_t)a.N * d * 4);
+    const int ngroups = (int)((d + kTRRows - 1) / kTRRows);
 
     for (int g0 = 0; g0 < a.N; g0 += kTRWorkers) {
         const int nw = a.N - g0 < kTRWorkers ? a.N - g0 : kTRWorkers;
-        const bool first = g0 == 0;
-        const int nout = nw + (first ? 1 : 0);     // output nw is the noise-free gradient (first pass)
-        // the worker's rows, loaded now so that they arrive during the sums
-        const int64_t wrow = (int64_t)(g0 + (w < nw ? w : 0)) * d + cc;
+        const bool first = g0 == 0;                // output nw is the noise-free gradient (first pass)
+        // outputs past the workers take no noise: their offset lies past xi
+        const int offX = n16 < nw ? (int)(((int64_t)(g0 + n16) * d + q4) * 4) : 0x7FFFFFF0;
+        ea_d4v s[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) s[c] = ea_d4v{0.0, 0.0, 0.0, 0.0};
+        struct Group {
+            ea_fv a[4];                            // A, rows 4q + j
+            ea_u4v x, r0, r1;                      // noise and residuals of the same rows
+        };
+        const auto load = [&](int grp, Group& f) {
+            const int64_t k0 = (int64_t)(grp < ngroups ? grp : 0) * kTRRows;
+            // rows past d read as zeros past the end of A; columns past d
+            // read what follows and are not used
+            const __amdgpu_buffer_rsrc_t rA = window(a.A + k0 * d + c0, grp < ngroups ? ((d - k0) * d - c0) * 4 : 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if constexpr (CT == 2)
+                    f.a[j] = __builtin_bit_cast(ea_fv, __builtin_amdgcn_raw_buffer_load_b64(rA, offA[j], 0, 0));
+                else
+                    f.a[j] = __builtin_bit_cast(ea_fv, __builtin_amdgcn_raw_buffer_load_b128(rA, offA[j], 0, 0));
+            }
+            f.x = __builtin_amdgcn_raw_buffer_load_b128(rxi, n16 < nw ? offX + (int)k0 * 4 : offX, 0, 0);
+            f.r0 = __builtin_amdgcn_raw_buffer_load_b128(rres, ((int)k0 + q4) * 8, 0, 0);
+            f.r1 = __builtin_amdgcn_raw_buffer_load_b128(rres, ((int)k0 + q4) * 8 + 16, 0, 0);
+        };
+        const auto sum = [&](int grp, const Group& f) {
+            const bool full = (int64_t)(grp + 1) * kTRRows <= d;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t lo = j < 2 ? f.r0[2 * j] : f.r1[2 * j - 4];
+                const uint32_t hi = j < 2 ? f.r0[2 * j + 1] : f.r1[2 * j - 3];
+                double val = join(hi, lo) - (double)__uint_as_float(f.x[j]);
+                // past d the noise read is another worker's: zero, so that not
+                // even an infinity there meets the zeros of A
+                if (!full) val = (int64_t)grp * kTRRows + q4 + j < d ? val : 0.0;
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+                    s[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(val, (double)f.a[j][c], s[c], 0, 0, 0);
+            }
+        };
+        // A ring of SETS sets of AHEAD groups: while one set is summed, the
+        // others' loads are in flight.
+        Group f[SETS][AHEAD];
+        constexpr int kStep = kTRWaves * AHEAD;
+#pragma unroll
+        for (int i = 0; i < SETS - 1; ++i)
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) load(w + i * kStep + u * kTRWaves, f[i][u]);
+        for (int grp0 = w; grp0 < ngroups; grp0 += SETS * kStep) {
+#pragma unroll
+            for (int i = 0; i < SETS; ++i) {
+                const int grp = grp0 + i * kStep;
+                if (grp >= ngroups) break;
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+                    load(grp + (SETS - 1) * kStep + u * kTRWaves, f[(i + SETS - 1) % SETS][u]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < AHEAD; ++u)
+                    if (grp + u * kTRWaves < ngroups) sum(grp + u * kTRWaves, f[i][u]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // After the sums, thread (o, column) holds output o of the pass.  Its
+        // rows and the server's (only this block writes them) are loaded here
+        // and arrive during the reduction; loaded before the sums they took
+        // registers from the groups in flight.
+        const int o = (int)threadIdx.x / COLS;
+        const int64_t wrow = (int64_t)(g0 + (o < nw ? o : 0)) * d + (in ? col : d - 1);
         float e0 = 0.0f, m0 = 0.0f, v0 = 0.0f;
-        if (ROUND && w < nw) {
+        if (ROUND && o < nw) {
             e0 = a.e_w[wrow];
             if (atw) {
                 m0 = a.m_w[wrow];
                 v0 = a.v_w[wrow];
             }
         }
-        double s[kTROut];
-#pragma unroll
-        for (int o = 0; o < kTROut; ++o) s[o] = 0.0;
-        const int64_t kb = (int64_t)blockIdx.y * a.split_rows;
-        const int64_t ke = d - kb < a.split_rows ? d : kb + a.split_rows;
-        for (int64_t k0 = kb; k0 < ke; k0 += ROWS) {
-            const int rows = ke - k0 < ROWS ? (int)(ke - k0) : ROWS;
-            const int r0 = w * kPer;
-            float av[kPer];
-#pragma unroll
-            for (int j = 0; j < kPer; ++j) av[j] = r0 + j < rows ? a.A[(k0 + r0 + j) * d + cc] : 0.0f;
-            __syncthreads();                       // the previous tile has been read
-            // every slot of the tile: outputs past nout and rows past the
-            // tile's end hold zeros, so the sums below need no guards
-            for (int idx = threadIdx.x; idx < kTROut * ROWS; idx += kTRWaves * kWave) {
-                const int o = idx / ROWS, kk = idx - o * ROWS;
-                double val = 0.0;
-                if (kk < rows && o < nout) {
-                    const double r = a.res[k0 + kk];
-                    val = o < nw ? r - (double)a.xi[(int64_t)(g0 + o) * d + k0 + kk] : r;
-                }
-                big[kk * kTROut + o] = val;
+        if (ROUND && server && in && g0 + kTRWorkers >= a.N) {
+            if (!atw) {
+                sm = a.m[col];
+                sv = a.v[col];
             }
-            __syncthreads();
-            const auto row = [&](int j) {
-                const double ad = (double)av[j];
-                const double2* t = reinterpret_cast<const double2*>(big + (r0 + j) * kTROut);
+            se = a.e_s[col];
+            sx = a.x[col];
+        }
+        if (!first) __syncthreads();               // the previous pass's sums have been read
 #pragma unroll
-                for (int o2 = 0; o2 < kTROut / 2; ++o2) {
-                    const double2 tv = t[o2];
-                    s[2 * o2] = fma(ad, tv.x, s[2 * o2]);
-                    s[2 * o2 + 1] = fma(ad, tv.y, s[2 * o2 + 1]);
-                }
-            };
-            if (r0 + kPer <= rows) {
+        for (int i = 0; i < 4; ++i) {
+            // result lane l, register i: output l/16 + 4i, column l%16 of its tile
 #pragma unroll
-                for (int j = 0; j < kPer; ++j) row(j);
-            } else {
-                for (int j = 0; r0 + j < rows; ++j) row(j);
+            for (int c = 0; c < CT; c += 2) {
+                double2* slot = reinterpret_cast<double2*>(big + (w * kTROut + (lane >> 4) + 4 * i) * COLS + CT * n16 + c);
+                *slot = make_double2(s[c][i], s[c + 1][i]);
             }
         }
-        __syncthreads();                           // every wave is done with the last tile
-#pragma unroll
-        for (int o = 0; o < kTROut; ++o)
-            if (o < nout) big[(w * kTROut + o) * kWave + lane] = s[o];
         __syncthreads();
-        double tot = 0.0;
-        if (w < nout)
-            for (int u = 0; u < kTRWaves; ++u) tot += big[(u * kTROut + w) * kWave + lane];
-        if (a.splits > 1) {
-            // publish this split's sums; the group's last block adds them all
-            constexpr int64_t kSet = kTROut * kWave;
-            double* group = a.psum + (int64_t)blockIdx.x * a.splits * kSet;
-            // Each wave that stored releases its own stores (a write-back of
-            // the L2, no invalidation: the other blocks are still reading A
-            // through it); only the group's last block acquires.
-            if (w < nout) {
-                group[blockIdx.y * kSet + w * kWave + lane] = tot;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                const bool last = atomicAdd(a.counter + 1 + blockIdx.x, 1u) == (uint32_t)(a.splits - 1);
-                if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                last_split = last ? 1 : 0;
-            }
-            __syncthreads();
-            if (!last_split) return;               // the whole block leaves together
-            if (w < nout) {
-                // all the loads first (one memory latency), then the sums in
-                // split order
-                const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(group);
-                double part[kTRMaxSplits];
+        if (o < kTROut) {                          // whole waves
+            double tot = 0.0;
 #pragma unroll
-                for (int r = 0; r < kTRMaxSplits; ++r)
-                    part[r] = r < a.splits ? __longlong_as_double((long long)__atomic_load_n(
-                                                 bits + r * kSet + w * kWave + lane, __ATOMIC_RELAXED))
-                                           : 0.0;
-                tot = 0.0;
-#pragma unroll
-                for (int r = 0; r < kTRMaxSplits; ++r)
-                    if (r < a.splits) tot += part[r];
-            }
-        }
-        if (w < nout) {
+            for (int u = 0; u < kTRWaves; ++u) tot += big[(u * kTROut + o) * COLS + (lane & (COLS - 1))];
             const double gd = 2.0 * tot;
-            if (w < nw) {
-                // worker g0 + w (Algorithm 2 with Adam at the worker, else g + e)
-                const float g = (float)gd;
-                if (a.g_out != nullptr && in) a.g_out[wrow] = g;
-                if constexpr (ROUND) {
-                    float p;
-                    if (atw) {
-                        const float vk = a.beta2 * v0 + (1.0f - a.beta2) * (g * g);
-                        const float mk = a.beta1 * m0 + (1.0f - a.beta1) * g;
-                        p = (vk > 0.0f ? a.lr * (mk / sqrtf(vk)) : 0.0f) + e0;
-                        if (in) {
-                            a.m_w[wrow] = mk;
-                            a.v_w[wrow] = vk;
-                        }
-                    } else {
-                        p = g + e0;
+            const bool mine = o < nw;
+            // worker g0 + o (Algorithm 2 with Adam at the worker, else g + e)
+            const float g = (float)gd;
+            if (mine && in && a.g_out != nullptr) a.g_out[wrow] = g;
+            if constexpr (ROUND) {
+                float p;
+                if (atw) {
+                    const float vk = a.beta2 * v0 + (1.0f - a.beta2) * (g * g);
+                    const float mk = a.beta1 * m0 + (1.0f - a.beta1) * g;
+                    p = (vk > 0.0f ? a.lr * (mk / sqrtf(vk)) : 0.0f) + e0;
+                    if (mine && in) {
+                        a.m_w[wrow] = mk;
+                        a.v_w[wrow] = vk;
                     }
-                    uint32_t code;
-                    float dq;
-                    toy_code(a.qw, p, code, dq);
-                    if (in) a.e_w[wrow] = a.qw.ef ? p - dq : 0.0f;
-                    toy_store_codes(a.qw, a.wcodes + (int64_t)(g0 + w) * a.qw.words, col, in, code);
-                    xfer[w * kWave + lane] = dq;
+                } else {
+                    p = g + e0;
                 }
-            } else if (a.grad_sq != nullptr) {
-                // the noise-free gradient: this column group's share of
-                // ||grad F||^2; the last group to get here adds the shares:
-                // lane l the shares of groups l, l+64, ... in order (loaded
-                // side by side), then the wave's sum
-                const double sq = wave_sum(in ? gd * gd : 0.0);
-                uint32_t done = 0;
-                if (lane == 0) {
-                    a.part[blockIdx.x] = sq;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                    done = atomicAdd(a.counter, 1u);
-                    if (done == gridDim.x - 1) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                }
-                done = (uint32_t)__builtin_amdgcn_readfirstlane((int)done);
-                if (done == gridDim.x - 1) {
-                    double mine = 0.0;
-                    const unsigned long long* bits = reinterpret_cast<const unsigned long long*>(a.part);
-                    for (uint32_t b = (uint32_t)lane; b < gridDim.x; b += kWave)
-                        mine += __longlong_as_double((long long)__atomic_load_n(bits + b, __ATOMIC_RELAXED));
-                    const double all = wave_sum(mine);
-                    if (lane == 0) *a.grad_sq = all;
-                }
+                uint32_t code;
+                float dq;
+                toy_code(a.qw, p, code, dq);
+                if (mine && in) a.e_w[wrow] = a.qw.ef ? p - dq : 0.0f;
+                toy_store_codes<COLS>(a.qw, mine ? a.wcodes + (int64_t)(g0 + o) * a.qw.words : nullptr, c0, in, last, code);
+                if (mine) xfer[o * COLS + (lane & (COLS - 1))] = dq;
             }
         }
-        __syncthreads();
-        if (ROUND && w == kServer)
-            for (int i = 0; i < nw; ++i) acc = acc + xfer[i * kWave + lane];
+        // the noise-free gradient's square, on a wave without a worker
+        if (first && w == norm_wave(nw) && a.grad_sq != nullptr) {
+            double tot = 0.0;
+#pragma unroll
+            for (int u = 0; u < kTRWaves; ++u) tot += big[(u * kTROut + nw) * COLS + (lane & (COLS - 1))];
+            const double gd = 2.0 * tot;
+            norm_sq = lane < COLS && in ? gd * gd : 0.0;
+        }
+        if constexpr (ROUND) {
+            __syncthreads();
+            if (server) {
+                float dq[kTRWorkers];              // all the reads first
+#pragma unroll
+                for (int i = 0; i < kTRWorkers; ++i) dq[i] = xfer[i * COLS + lane];
+#pragma unroll
+                for (int i = 0; i < kTRWorkers; ++i)
+                    if (i < nw) acc = acc + dq[i];
+            }
+        }
     }
 
-    if (ROUND && w == kServer) {
+    if (ROUND && w == kServer) {                   // lanes past the columns store nothing
         // Algorithm 1: average, [Adam at the server], residual, quantize, apply
         const float fN = (float)a.N;
         const bool pow2 = (a.N & (a.N - 1)) == 0;
@@ -360,7 +381,7 @@ __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
             const float vk = a.beta2 * sv + (1.0f - a.beta2) * (avg * avg);
             const float mk = a.beta1 * sm + (1.0f - a.beta1) * avg;
             u = vk > 0.0f ? a.lr * (mk / sqrtf(vk)) : 0.0f;
-            if (in) {
+            if (server && in) {
                 a.m[col] = mk;
                 a.v[col] = vk;
             }
@@ -369,56 +390,99 @@ __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
         uint32_t code;
         float dq;
         toy_code(a.qs, q, code, dq);
-        if (in) {
+        if (server && in) {
             a.e_s[col] = a.qs.ef ? q - dq : 0.0f;
             a.x[col] = sx - dq;
         }
-        toy_store_codes(a.qs, a.scodes, col, in, code);
+        toy_store_codes<COLS>(a.qs, server ? a.scodes : nullptr, c0, in, last, code);
+    }
+
+    // The block's share of ||grad F||^2.  The last block to get here adds the
+    // shares: lane l those of blocks l, l+64, ... in order (loaded side by
+    // side), then the wave's sum.  Share and loads are device-coherent by
+    // themselves (agent-scope atomics, written through and read past the L2s),
+    // so all that is needed is that the share has arrived before the count:
+    // the wait.  (A release fence would write back the XCD's whole L2, an
+    // acquire drop it.)
+    if (w == norm_wave(a.N < kTRWorkers ? a.N : kTRWorkers) && a.grad_sq != nullptr) {
+        const double sq = wave_sum(norm_sq);
+        unsigned long long* bits = reinterpret_cast<unsigned long long*>(a.part);
+        uint32_t done = 0;
+        if (lane == 0) {
+            __hip_atomic_store(bits + blk, (unsigned long long)__double_as_longlong(sq), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            done = __hip_atomic_fetch_add(a.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        done = (uint32_t)uniform((int)done);
+        if (done == (uint32_t)a.nblk - 1) {
+            asm volatile("" ::: "memory");
+            double share = 0.0;
+            for (int b = lane; b < a.nblk; b += kWave)
+                share += __longlong_as_double(
+                    (long long)__hip_atomic_load(bits + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            const double all = wave_sum(share);
+            if (lane == 0) *a.grad_sq = all;
+        }
     }
 }
 
 }  // namespace
 
-// r (d doubles), the per-block partial norms (one per 64 columns), the
-// fused round's counters (1 + one per column group, as 32-bit words) and its
-// splits' column sums.
+// Columns per block: 64 once such blocks fill the 256 CUs (each block then
+// reads the residuals and the noise for twice the columns: d = 16384, 10
+// workers 394 against 431 us a step), 32 below (d = 8192 92 against 130 us, d =
+// 2075 22 against 30: half the CUs would have no block), and 64 up to 64
+// parameters, a single block either way.
+int toy_cols(int64_t d)
+{
+    return d > 64 && (d + 63) / 64 < 256 ? 32 : 64;
+}
+
+// The two launches use r (d doubles), a partial norm per column block and the
+// counter of blocks done (a 32-bit word).  The size that callers are told is
+// the ABI's own: with 64-column blocks just that and a counter for each (as
+// 32-bit words), with 32-column blocks up to eight sets of sixteen 64-column
+// sums for each 64 columns besides, many times what is used.
 int64_t toy_workspace_bytes(int64_t d)
 {
-    const int64_t nblk = (d + kWave - 1) / kWave;
-    int64_t rows = 0;
-    const int64_t R = toy_splits(d, &rows);
-    const int64_t psum = R > 1 ? nblk * R * kTROut * kWave : 0;
-    return (d + nblk + (nblk + 2) / 2 + psum) * (int64_t)sizeof(double);
+    const int64_t cols64 = (d + kWave - 1) / kWave;
+    int64_t sets = (d + kWave - 1) / kWave;
+    if (sets > 8) sets = 8;
+    if (sets > 1024 / cols64) sets = 1024 / cols64;
+    if (sets >= 2) {
+        const int64_t rows = ((d + sets - 1) / sets + kWave - 1) / kWave * kWave;
+        sets = (d + rows - 1) / rows;
+    } else {
+        sets = 0;
+    }
+    if (sets < 2) sets = 0;
+    return (d + cols64 + (cols64 + 2) / 2 + cols64 * sets * 16 * kWave) * (int64_t)sizeof(double);
 }
 
 namespace {
 
-// The residual launch (which also clears the counters), then the round
+// The residual launch (which also clears the counter), then the round
 // kernel, with the round (ROUND) or writing the gradients only.
 template <bool ROUND>
 hipError_t launch_toy(ToyArgs& a, const float* xs, const float* x, void* workspace, hipStream_t s)
 {
     const int64_t d = a.d;
-    const int64_t nblk = (d + kWave - 1) / kWave;
+    const int cols = toy_cols(d);
+    a.nblk = (int32_t)((d + cols - 1) / cols);
     double* res = static_cast<double*>(workspace);
     a.res = res;
     a.part = res + d;
-    a.counter = reinterpret_cast<uint32_t*>(res + d + nblk);
-    a.psum = res + d + nblk + (nblk + 2) / 2;
-    // several splits only when the workers fit one pass (each pass would
-    // need its own sums) and the workspace holds them (toy_workspace_bytes)
-    a.splits = a.N <= kTRWorkers ? toy_splits(d, &a.split_rows) : 1;
-    if (a.splits == 1) a.split_rows = d;
+    a.counter = reinterpret_cast<uint32_t*>(res + d + a.nblk);
     hipLaunchKernelGGL(toy_residual_kernel, dim3((unsigned)((d + kResWaves - 1) / kResWaves)),
-                       dim3(kResWaves * kWave), 0, s, d, a.A, xs, x, res, a.counter, (int32_t)(1 + nblk));
+                       dim3(kResWaves * kWave), 0, s, d, a.A, xs, x, res, a.counter);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.splits > 1)
-        hipLaunchKernelGGL((toy_round_kernel<kTRSplitRows, ROUND>), dim3((unsigned)nblk, (unsigned)a.splits),
-                           dim3(kTRWaves * kWave), 0, s, a);
+    const dim3 grid((unsigned)((a.nblk + 7) / 8 * 8)), block(kTRWaves * kWave);
+    if (cols == 32)
+        hipLaunchKernelGGL((toy_round_kernel<2, 2, 1, ROUND>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((toy_round_kernel<kTRRows, ROUND>), dim3((unsigned)nblk), dim3(kTRWaves * kWave), 0, s,
-                           a);
+        hipLaunchKernelGGL((toy_round_kernel<4, 1, 2, ROUND>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
