@@ -386,8 +386,12 @@ __device__ __forceinline__ float deq_of(const QDev& q, const float* lut, uint32_
 // rows, else four 4-byte ones per lane with a compare each; the ragged last
 // tile in a launch of its own): see step_kernel.
 //
-// Every vector the round touches is streamed once per round and is far larger
-// than the caches, so loads and stores carry the non-temporal hint.
+// Stores carry the non-temporal hint: every vector is written once a round.
+// Loads carry it (STREAM) where a vector is read once.  (Without it, rounds whose
+// rows fit the 256 MB memory-side cache with what else a program holds gain up
+// to 10%, 8M row elements 26.8 -> 24.3 us, and larger ones lose 8%, BERT-sized
+// 4.54 -> 4.92 ms; a branch on the size around the loads cost most of the
+// gain.)
 // ---------------------------------------------------------------------------
 typedef uint32_t ea_u2v __attribute__((ext_vector_type(2)));
 typedef uint32_t ea_u4v __attribute__((ext_vector_type(4)));
@@ -413,9 +417,11 @@ __device__ __forceinline__ Row row_of(const float* p, int left)
 }
 
 // Chunk `ch` of the span, this lane's four elements.
+template <bool STREAM = true>
 __device__ __forceinline__ float4 ld4(const Row& row, int ch)
 {
-    const ea_u4v v = __builtin_amdgcn_raw_buffer_load_b128(row.r, lane_id() * 16 + ch * (kChunk * 4), 0, kNonTemporal);
+    const ea_u4v v = __builtin_amdgcn_raw_buffer_load_b128(row.r, lane_id() * 16 + ch * (kChunk * 4), 0,
+                                                           STREAM ? kNonTemporal : 0);
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 

@@ -37,6 +37,14 @@ const HalfKernel kHalf[] = {
     half<QCt<Q_DET, 3, S_MAX, 2>>(),
     half<QCt<Q_POW2, 4, S_MAX, 0>>(),
     half<QCt<Q_NONE, 32, S_MAX, 0>>(),
+    // one bucket over the vector: the scale is given, whichever norm it is
+    half<QCt<Q_SCALED_SIGN, 1, S_MAX, 0>>(),
+    half<QCt<Q_STOCH, 1, S_MAX, 0>>(),
+    half<QCt<Q_STOCH, 2, S_MAX, 0>>(),
+    half<QCt<Q_STOCH, 4, S_MAX, 0>>(),
+    half<QCt<Q_STOCH, 8, S_MAX, 0>>(),
+    half<QCt<Q_DET, 2, S_MAX, 0>>(),
+    half<QCt<Q_DET, 3, S_MAX, 0>>(),
 };
 
 }  // namespace

@@ -36,8 +36,10 @@ struct StepArgs {
     uint64_t* scodes;         // [qs.words]
     float* sscales;           // [qs.nscales]
     // one-bucket workspace
-    double* wpart;            // [N][ntiles] per-tile partial norms (qw one bucket)
-    double* spart;            // [ntiles]    per-tile partial norms (qs one bucket)
+    double* wpart;            // [N][wnp] partial norms of the workers' vectors (qw one bucket)
+    double* spart;            // [snp] partial norms of the server's vector (qs one bucket)
+    int64_t wnp, snp;         // partials per vector
+    int32_t from_parts;       // every wave forms one-bucket scales from the partials itself
     float* ubuf;              // [d] server input / aggregate output
     int64_t tile0;            // fused round: the launch's first tile
     int32_t worker;           // split calls: worker index (Philox stream)
@@ -84,10 +86,13 @@ const HalfKernel* half_kernels_c1(int* n);
 const HalfKernel* half_kernels_c2(int* n);
 const HalfKernel* half_kernels_c4(int* n);
 const HalfKernel* half_kernels_c8(int* n);
-hipError_t launch_worker_partials(const StepArgs& a, int C, int i0, int i1, hipStream_t s);
+hipError_t launch_worker_partials(const StepArgs& a, int C, int nworkers, hipStream_t s);
 hipError_t launch_server_partials(const StepArgs& a, int C, hipStream_t s);
-hipError_t launch_finalize(const double* part, int64_t ntiles, int32_t norm, int64_t n, float* out,
+hipError_t launch_finalize(const double* part, int64_t nparts, int32_t norm, int64_t n, float* out,
                            int64_t out_stride, int nvec, hipStream_t s);
+// Partial norms of one vector of ntiles tiles: one per block of kWavesPerBlock
+// tiles from the partials kernels, one per tile from the fused round.
+inline int64_t block_parts(int64_t ntiles) { return (ntiles + kWavesPerBlock - 1) / kWavesPerBlock; }
 hipError_t launch_worker(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_aggregate(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_server(const StepArgs& a, int C, hipStream_t s);

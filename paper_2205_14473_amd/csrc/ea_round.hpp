@@ -31,6 +31,22 @@ namespace ea {
 
 namespace {
 
+// The scale of a one-bucket quantizer from the vector's n partial norms, the
+// same in every lane.  While they are few, each wave that needs the scale
+// forms it (a few loads from L2 and a wave sum, beside the loads of its rows)
+// instead of a launch of their own doing it once; `store` writes it out.
+__device__ __forceinline__ float scale_of_parts(const double* __restrict__ part, int64_t n, int norm, int64_t d,
+                                                float* scale, bool store)
+{
+    double v = 0.0;
+    for (int j = lane_id(); j < (int)n; j += kWave) v = norm == S_MAX ? fmax(v, part[j]) : v + part[j];
+    const double S = norm == S_MAX ? 0.0 : wave_sum(v);
+    const float M = norm == S_MAX ? wave_max((float)v) : 0.0f;
+    const float s = scale_from(norm, S, M, d);
+    if (store && lane_id() == 0) *scale = s;
+    return s;
+}
+
 // Largest number of waves in a block of the fused round (one worker each):
 // wide tiles need more registers per wave, so their blocks are narrower.
 #ifndef EA_WIDE_TILE_WAVES
@@ -1138,16 +1154,16 @@ __device__ __forceinline__ WorkerSpan worker_span(const StepArgs& a, const float
 }
 
 // The tile that starts at chunk ch0 of the span.
-template <int C, int PL>
+template <int C, int PL, bool STREAM = true>
 __device__ __forceinline__ void load_worker(const StepArgs& a, const WorkerSpan& s, int ch0, WorkerRows<C>& r)
 {
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        r.g[ch] = ld4(s.g, ch0 + ch);
-        r.e[ch] = ld4(s.e, ch0 + ch);
+        r.g[ch] = ld4<STREAM>(s.g, ch0 + ch);
+        r.e[ch] = ld4<STREAM>(s.e, ch0 + ch);
         if (placement_of<PL>(a) == AT_WORKER) {
-            r.m[ch] = ld4(s.m, ch0 + ch);
-            r.v[ch] = ld4(s.v, ch0 + ch);
+            r.m[ch] = ld4<STREAM>(s.m, ch0 + ch);
+            r.v[ch] = ld4<STREAM>(s.v, ch0 + ch);
         }
     }
 }
@@ -1383,11 +1399,10 @@ __device__ __forceinline__ bool tile_pos(const StepArgs& a, TilePos& t)
 // slot.
 template <int C, class QW, int PL>
 __device__ __forceinline__ void worker_compute(const StepArgs& a, const TilePos& t, const float* lut_w, int i,
-                                               const WorkerSpan& s, int ch0, WorkerRows<C>& r, WordSink& sink,
-                                               float4* slot)
+                                               const WorkerSpan& s, int ch0, WorkerRows<C>& r, float gs,
+                                               WordSink& sink, float4* slot)
 {
     const int lane = lane_id();
-    const bool wglobal = has_scale<QW>(a.qw) && QW::cpb(a.qw) == 0;
     float4 p[C], dq[C];
     if constexpr (select_first<QW, C>()) {
         // the selection and the code words first, while the rows arrive; the
@@ -1408,7 +1423,6 @@ __device__ __forceinline__ void worker_compute(const StepArgs& a, const TilePos&
     } else {
         worker_p<C, PL>(a, r, p);
         store_moments<C, PL>(a, s, ch0, r);
-        const float gs = wglobal ? a.wscales[(int64_t)i * a.qw.nscales] : 0.0f;
         quantize_tile<C, QW>(a.qw, lut_w, p, t.base, t.left, a.k0, a.k1, a.t, (uint32_t)i, gs,
                              a.wcodes + (int64_t)i * a.qw.words, a.wscales + (int64_t)i * a.qw.nscales, sink, dq);
     }
@@ -1429,6 +1443,13 @@ __device__ __forceinline__ void gather_group(const float4* slot, int cnt, float4
     }
 }
 
+// Scale of the one-bucket worker quantizer for message row i of the launch.
+__device__ __forceinline__ float worker_scale(const StepArgs& a, int64_t i, bool store)
+{
+    float* scale = a.wscales + i * a.qw.nscales;
+    return a.from_parts ? scale_of_parts(a.wpart + i * a.wnp, a.wnp, a.qw.norm, a.d, scale, store) : *scale;
+}
+
 // Worker i on the block's K consecutive tiles: all tiles' rows are loaded
 // first, so the later tiles' loads are in flight while the first is
 // compressed; the codes of the tiles leave through one sink, as one piece.
@@ -1444,10 +1465,13 @@ __device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&
 #pragma unroll
     for (int k = 0; k < K; ++k)
         if constexpr (!select_first<QW, C>()) load_worker<C, PL>(a, s, k * C, r[k]);
+    float gs = 0.0f;
+    if (has_scale<QW>(a.qw) && QW::cpb(a.qw) == 0) gs = worker_scale(a, i, base == 0);
     WordSink sink = message_sink<QW>(a.qw, a.wcodes + (int64_t)i * a.qw.words, base, left);
 #pragma unroll
     for (int k = 0; k < K; ++k)
-        worker_compute<C, QW, PL>(a, tp[k], lut_w, i, s, k * C, r[k], sink, slots + ((int64_t)k * G + w) * C * kWave);
+        worker_compute<C, QW, PL>(a, tp[k], lut_w, i, s, k * C, r[k], gs, sink,
+                                  slots + ((int64_t)k * G + w) * C * kWave);
     sink.flush();
 }
 
@@ -1734,7 +1758,7 @@ __global__ __launch_bounds__(kBlock) void worker_kernel(StepArgs a)
     load_worker<C, -1>(a, s, 0, r);
     worker_p<C, -1>(a, r, p);
     store_moments<C, -1>(a, s, 0, r);
-    const float gs = wglobal ? a.wscales[0] : 0.0f;
+    const float gs = wglobal ? worker_scale(a, 0, t.tile == 0) : 0.0f;
     WordSink sink = message_sink<QW>(a.qw, a.wcodes, t.base, t.left);
     quantize_tile<C, QW>(a.qw, lut_w, p, t.base, t.left, a.k0, a.k1, a.t, (uint32_t)a.worker, gs, a.wcodes, a.wscales,
                          sink, dq);
@@ -1838,7 +1862,9 @@ __global__ __launch_bounds__(kBlock) void server_kernel(StepArgs args)
     float4 q[C], dq[C];
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) q[ch] = add4(ld4(u, ch), ld4(e, ch));
-    const float gs = sglobal ? a.sscales[0] : 0.0f;
+    float gs = 0.0f;
+    if (sglobal)
+        gs = a.from_parts ? scale_of_parts(a.spart, a.snp, a.qs.norm, a.d, a.sscales, t.tile == 0) : a.sscales[0];
     WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base, t.left);
     quantize_tile<C, QS>(a.qs, lut_s, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream, gs, a.scodes, a.sscales, sink,
                          dq);
@@ -1937,8 +1963,8 @@ __device__ __forceinline__ int64_t block_slot(const StepArgs& a)
     return g * grp + (i % 8) * R + i / 8;
 }
 
-// The fused round.  With a one-bucket Q_w the worker scales are read from
-// wscales (computed beforehand); with a one-bucket Q_s the block stops after
+// The fused round.  With a one-bucket Q_w the worker scales come from partial
+// norms computed beforehand (worker_scale); with a one-bucket Q_s the block stops after
 // the server input, which it leaves in ubuf with per-tile partial norms.
 //
 // MW > 0 overrides the minimum waves per SIMD of the launch bounds (the
