@@ -186,12 +186,15 @@ const HalfKernel* find_half_for(const QDev& q, int C)
     const bool sparse = q.kind == Q_TOPK || q.kind == Q_RANDK;
     if (q.cpb != 0 && q.cpb != C) return nullptr;
     const int norm = q.cpb == 0 || sparse ? S_MAX : q.norm;   // as the tables write it
-    int n = 0;
-    const HalfKernel* t = C == 1 ? half_kernels_c1(&n) : C == 2 ? half_kernels_c2(&n)
-                        : C == 4 ? half_kernels_c4(&n) : C == 8 ? half_kernels_c8(&n) : nullptr;
-    for (int i = 0; i < n; ++i) {
-        const HalfKernel& h = t[i];
-        if (h.C == C && h.wkind == q.kind && h.wbits == q.bits && h.wnorm == norm && h.wcpb == q.cpb) return &h;
+    for (int wide = 0; wide < 2; ++wide) {
+        int n = 0;
+        const HalfKernel* t = wide ? (C <= 2 ? half_kernels_wide_c12(&n) : half_kernels_wide_c48(&n))
+                            : C == 1 ? half_kernels_c1(&n) : C == 2 ? half_kernels_c2(&n)
+                            : C == 4 ? half_kernels_c4(&n) : C == 8 ? half_kernels_c8(&n) : nullptr;
+        for (int i = 0; i < n; ++i) {
+            const HalfKernel& h = t[i];
+            if (h.C == C && h.wkind == q.kind && h.wbits == q.bits && h.wnorm == norm && h.wcpb == q.cpb) return &h;
+        }
     }
     return nullptr;
 }

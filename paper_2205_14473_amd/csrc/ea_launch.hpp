@@ -86,6 +86,8 @@ const HalfKernel* half_kernels_c1(int* n);
 const HalfKernel* half_kernels_c2(int* n);
 const HalfKernel* half_kernels_c4(int* n);
 const HalfKernel* half_kernels_c8(int* n);
+const HalfKernel* half_kernels_wide_c12(int* n);
+const HalfKernel* half_kernels_wide_c48(int* n);
 hipError_t launch_worker_partials(const StepArgs& a, int C, int nworkers, hipStream_t s);
 hipError_t launch_server_partials(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_finalize(const double* part, int64_t nparts, int32_t norm, int64_t n, float* out,

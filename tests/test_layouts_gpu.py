@@ -22,6 +22,7 @@ STOCH = lambda k, s, b: qfields(O.Q_STOCH_UNIFORM, k, s, bucket=b)  # noqa: E731
 DET = lambda k, b: qfields(O.Q_DET_UNIFORM, k, bucket=b)  # noqa: E731
 SPARSE = lambda kind, keep, b: qfields(kind, bucket=b, keep=keep)  # noqa: E731
 POW2 = qfields(O.Q_POW2, kmin=-17, kmax=-11)
+POW2W = qfields(O.Q_POW2, kmin=-20, kmax=-6)      # 5-bit codes
 NONE = qfields(O.Q_NONE)
 PAD = 64
 
@@ -49,7 +50,8 @@ CASES = [
     (2048, SPARSE(O.Q_RANDK, 64, 2048), SPARSE(O.Q_RANDK, 64, 2048)), (1024, SPARSE(O.Q_RANDK, 40, 1024), SPARSE(O.Q_RANDK, 40, 1024)),
     (1024, STOCH(8, O.SCALE_MAX, 1024), STOCH(8, O.SCALE_MAX, 1024)), (256, SIGN(256), SIGN(256)),
     (256, STOCH(4, O.SCALE_L2, 256), DET(3, 256)), (512, DET(3, 512), POW2), (512, POW2, NONE), (512, NONE, POW2),
-    (1024, DET(5, 256), STOCH(4, O.SCALE_L2, 1024)), (512, SIGN(0), DET(2, 0)), (2048, POW2, STOCH(1, O.SCALE_L2, 2048)),
+    (256, DET(8, 256), POW2W), (512, DET(4, 512), DET(7, 512)), (1024, DET(6, 1024), POW2W), (2048, POW2W, DET(5, 2048)),
+    (512, DET(5, 0), DET(8, 0)), (1024, DET(5, 256), STOCH(4, O.SCALE_L2, 1024)), (512, SIGN(0), DET(2, 0)), (2048, POW2, STOCH(1, O.SCALE_L2, 2048)),
 ]
 
 
