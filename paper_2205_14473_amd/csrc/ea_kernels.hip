@@ -224,7 +224,7 @@ const SymKernel* find_sym(const StepArgs& a, int C)
 // (with fewer workers than tiles the other waves only serve).  Fully
 // specialized 8-chunk tiles serve a whole-tile server bucket, or a
 // sparsifier's server side, on C waves, one chunk each (SplitServe,
-// SparseServe; whole and ragged tiles alike), so their blocks have C waves
+// SparseServe), so their blocks have C waves
 // at least.
 int step_waves(const StepArgs& a, int C, int K, const Special* sp, const SymKernel* sk, size_t limit)
 {

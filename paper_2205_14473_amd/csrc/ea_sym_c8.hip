@@ -16,7 +16,7 @@ namespace {
 #ifndef EA_SYM_C8_MIN_WAVES
 #define EA_SYM_C8_MIN_WAVES 2
 #endif
-// The sparsifiers' whole-tile kernels serve on eight waves and select on one
+// The sparsifiers' kernels serve on eight waves and select on one
 // (SparseServe), and fit in fewer registers.
 #ifndef EA_SYM_C8_TOPK_MIN_WAVES
 #define EA_SYM_C8_TOPK_MIN_WAVES 4
