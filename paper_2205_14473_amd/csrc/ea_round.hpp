@@ -87,9 +87,11 @@ __host__ __device__ constexpr int round_tiles_per_block(int C, bool lean)
 
 // Minimum waves per SIMD the compiler must leave room for (caps VGPRs).
 // Kernels with Adam at the server have no worker moments and need fewer
-// registers than the others.
+// registers than the others.  Uncapped, several of 4-chunk tiles take 131 to
+// 135, three waves instead of four (40M parameters, 16 workers: 8-bit
+// stochastic 2074 us against 1798, random-32 of 1024 2078 against 1725).
 #ifndef EA_C4_MIN_WAVES
-#define EA_C4_MIN_WAVES 1
+#define EA_C4_MIN_WAVES 4
 #endif
 #ifndef EA_C8_MIN_WAVES
 #define EA_C8_MIN_WAVES 3
@@ -125,11 +127,17 @@ __device__ __forceinline__ bool inside(int left, int ch, int k)
     return ch * kChunk + 4 * lane_id() + k < left;
 }
 
-// Marks a branch that only ragged tiles take: without it the compiler turns
-// the few selects inside into unconditional ones for every tile.
-__device__ __forceinline__ void ragged_only()
+// `left` for use inside a branch that few tiles take (ragged tiles, buckets of
+// zeros): opaque there, so the compiler neither turns the few selects inside
+// into unconditional ones nor forms their lane masks ahead of the branch, for
+// every tile.  (Formed ahead, eight masks a tile pushed other scalars into
+// vector lanes: Example 1, 3 bits in 2048-element buckets, 40M parameters, 16
+// workers 3404 -> 2775 us without.)
+__device__ __forceinline__ int rare(int left)
 {
-    asm volatile("; ragged tile");
+    left = uniform(left);
+    asm volatile("; rare tile" : "+s"(left));
+    return left;
 }
 
 template <int PL>
@@ -163,6 +171,39 @@ __device__ __forceinline__ StepArgs with_step(const StepArgs& in)
         a.lr = a.sched_alpha * r;
     }
     return a;
+}
+
+// The kernel's arguments (every kernel's first parameter is its StepArgs) read
+// anew from the argument segment.  The compiler otherwise loads them at the
+// kernel's start, sixteen registers at a time, and holds what the server side
+// needs through the workers' side by spilling it to vector lanes, whose reads
+// and writes take vector issue slots (with `rare` above, scalars spilled by the
+// BERT-sized round's kernel 64 -> 6, by the generic one of 8-chunk tiles 322 ->
+// 174).  40M parameters, 16 workers: 256-element worker and 2048-element server
+// buckets 5175 -> 4963 us, Example 1 with 3 bits in 2048-element buckets 2775 ->
+// 2654.
+__device__ __forceinline__ const StepArgs& reread_args()
+{
+    uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const StepArgs*)(const __attribute__((address_space(4))) StepArgs*)p;
+}
+
+// `a` with the server side's arguments read anew.
+__device__ __forceinline__ StepArgs server_args(const StepArgs& a)
+{
+    StepArgs b = a;
+    const StepArgs& k = reread_args();
+    b.m = k.m;
+    b.v = k.v;
+    b.e_s = k.e_s;
+    b.x = k.x;
+    b.scodes = k.scodes;
+    b.sscales = k.sscales;
+    b.spart = k.spart;
+    b.ubuf = k.ubuf;
+    b.qs = k.qs;
+    return b;
 }
 
 // ---------------------------------------------------------------------------
@@ -347,9 +388,9 @@ __device__ __forceinline__ uint32_t sparsify_tile(const QDev& q, const float4 (&
                 keys[ch][k] = topk ? (__float_as_uint(comp(p[ch], k)) & 0x7FFFFFFFu) : (rr[k] >> 8);
             // p is +0 past d, so top-k keys are 0 there already
             if (!topk && left < C * kChunk) {
-                ragged_only();
+                const int l = rare(left);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) keys[ch][k] = inside(left, ch, k) ? keys[ch][k] : 0u;
+                for (int k = 0; k < 4; ++k) keys[ch][k] = inside(l, ch, k) ? keys[ch][k] : 0u;
             }
         }
     }
@@ -760,12 +801,12 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
             // Zero or non-finite scale (uniform over the wave): the chunk is
             // sent as zero codes and dequantizes to zero.
             const uint32_t zc = zero_code_of<QT>(q);
+            const int l = rare(left);
             deq[ch] = zero4();
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const bool valid = inside(left, ch, k);
-                for (int pl = 0; pl < bits; ++pl)
-                    sink.put(__builtin_amdgcn_ballot_w64(valid && ((zc >> pl) & 1u) != 0u));
+                const uint64_t valid = __builtin_amdgcn_ballot_w64(inside(l, ch, k));
+                for (int pl = 0; pl < bits; ++pl) sink.put(((zc >> pl) & 1u) != 0u ? valid : 0);
             }
             continue;
         }
@@ -787,9 +828,9 @@ __device__ __forceinline__ void quantize_tile(const QDev& q, const float* lut, c
         for (int k = 0; k < 4; ++k) set_comp(deq[ch], k, deq_of<QT>(q, lut, cc[k], comp(p[ch], k), sc));
         // The code of 0 need not be 0 (it is for signs).
         if (kind != Q_SCALED_SIGN && ragged) {
-            ragged_only();
+            const int l = rare(left);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) cc[k] = inside(left, ch, k) ? cc[k] : 0u;
+            for (int k = 0; k < 4; ++k) cc[k] = inside(l, ch, k) ? cc[k] : 0u;
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -1347,11 +1388,11 @@ template <int C>
 __device__ __forceinline__ void zero_past_end(float4 (&q)[C], int left)
 {
     if (left == C * kChunk) return;
-    ragged_only();
+    const int l = rare(left);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch)
 #pragma unroll
-        for (int k = 0; k < 4; ++k) set_comp(q[ch], k, inside(left, ch, k) ? comp(q[ch], k) : 0.0f);
+        for (int k = 0; k < 4; ++k) set_comp(q[ch], k, inside(l, ch, k) ? comp(q[ch], k) : 0.0f);
 }
 
 // Partial norm of a tile (+0 past d), reduced over the wave (one-bucket
@@ -1372,14 +1413,22 @@ struct TilePos {
     int left;                 // elements of the tile inside d
 };
 
-// Position of tile `tile` of C chunks (`left` is 0 for one wholly past d).
+// Of a span with `left` elements inside d, those among the n from `start` on.
+__device__ __forceinline__ int part_left(int left, int start, int n)
+{
+    const int end = min(left, start + n);
+    return max(end, start) - start;
+}
+
+// Tile k of C chunks of the span that starts at tile `tile` and has `left`
+// elements inside d (t.left is 0 for one wholly past d).
 template <int C>
-__device__ __forceinline__ TilePos tile_at(const StepArgs& a, int64_t tile)
+__device__ __forceinline__ TilePos tile_of(int64_t tile, int k, int left)
 {
     TilePos t;
-    t.tile = tile;
-    t.base = tile * C * kChunk;
-    t.left = span_left(t.base, a.d, C * kChunk);
+    t.tile = tile + k;
+    t.base = t.tile * C * kChunk;
+    t.left = part_left(left, k * C * kChunk, C * kChunk);
     return t;
 }
 
@@ -1389,7 +1438,7 @@ __device__ __forceinline__ bool tile_pos(const StepArgs& a, TilePos& t)
 {
     const int64_t tile = a.tile0 + (int64_t)blockIdx.x * kWavesPerBlock + wave_id();
     if (tile >= a.ntiles) return false;
-    t = tile_at<C>(a, tile);
+    t = tile_of<C>(tile, 0, span_left(tile * C * kChunk, a.d, C * kChunk));
     return true;
 }
 
@@ -1455,11 +1504,10 @@ __device__ __forceinline__ float worker_scale(const StepArgs& a, int64_t i, bool
 // compressed; the codes of the tiles leave through one sink, as one piece.
 // Tile k's dequantized values go to slots + (k*G + w)*C*64.
 template <int C, int K, class QW, int PL>
-__device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&tp)[K], const float* lut_w, int i,
-                                             float4* slots, int G, int w)
+__device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&tp)[K], int left,
+                                             const float* lut_w, int i, float4* slots, int G, int w)
 {
     const int64_t base = tp[0].base, row = (int64_t)i * a.d;
-    const int left = span_left(base, a.d, K * C * kChunk);
     const WorkerSpan s = worker_span<PL>(a, a.g + row, a.e_w + row, a.m_w + row, a.v_w + row, base, left);
     WorkerRows<C> r[K];
 #pragma unroll
@@ -1522,7 +1570,7 @@ __device__ __forceinline__ void serve_split(const StepArgs& a, const TilePos& t,
     const bool serving = w < C;
     const int ch = serving ? w : 0;
     const int64_t base = t.base + (int64_t)ch * kChunk;
-    const int left = span_left(base, a.d, kChunk);
+    const int left = part_left(t.left, ch * kChunk, kChunk);
     const int norm = QS::norm(a.qs);
     ServerRows<1> sr;
     if (serving) load_server<1, PL>(a, base, left, true, true, sr);
@@ -1589,7 +1637,7 @@ __device__ __forceinline__ void serve_sparse(const StepArgs& a, const TilePos& t
     const bool serving = w < C;
     const int ch = serving ? w : 0;
     const int64_t base = t.base + (int64_t)ch * kChunk;
-    const int left = span_left(base, a.d, kChunk);
+    const int left = part_left(t.left, ch * kChunk, kChunk);
     ServerRows<1> sr;
     if (serving) load_server<1, PL>(a, base, left, true, true, sr);
     __syncthreads();                           // the last group's handoff is complete
@@ -1664,9 +1712,10 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, co
     // rows only before that tile's arithmetic.  (With the later tiles under a
     // branch it waited for every load, and for the stores issued since,
     // before the first tile and again before the second.)
+    const int left = span_left(tile0 * C * kChunk, a.d, K * C * kChunk);
     TilePos tp[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) tp[k] = tile_at<C>(a, tile0 + k);
+    for (int k = 0; k < K; ++k) tp[k] = tile_of<C>(tile0, k, left);
 
     constexpr int kAcc = kSplit ? 1 : C;
     float4 acc[kAcc];
@@ -1690,46 +1739,47 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, co
     float4* slots;
     for (; g0 + G < a.N; g0 += G, buf ^= a.one_buffer ? 0 : 1) {
         slots = xfer + buf * per_buf;
-        worker_round<C, K, QW, PL>(a, tp, lut_w, g0 + w, slots, G, w);
+        worker_round<C, K, QW, PL>(a, tp, left, lut_w, g0 + w, slots, G, w);
         __syncthreads();
         gather(slots, G);
         if (a.one_buffer) __syncthreads();
     }
     slots = xfer + buf * per_buf;
-    if (g0 + w < a.N) worker_round<C, K, QW, PL>(a, tp, lut_w, g0 + w, slots, G, w);
+    if (g0 + w < a.N) worker_round<C, K, QW, PL>(a, tp, left, lut_w, g0 + w, slots, G, w);
+    const StepArgs b = server_args(a);
     if constexpr (kSplit) {
-        if constexpr (kSparse) serve_sparse<C, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0]);
-        else serve_split<C, QS, PL>(a, tp[0], lut_s, slots, a.N - g0, acc[0], red);
+        if constexpr (kSparse) serve_sparse<C, QS, PL>(b, tp[0], lut_s, slots, a.N - g0, acc[0]);
+        else serve_split<C, QS, PL>(b, tp[0], lut_s, slots, a.N - g0, acc[0], red);
         return;
     } else {
-    const TilePos t = tile_at<C>(a, tile0 + (w < K ? w : 0));
+    const TilePos t = tile_of<C>(tile0, w < K ? w : 0, left);
     ServerRows<C> sr;
-    if (w < K) load_server<C, PL>(a, t.base, t.left, true, !sglobal, sr);
+    if (w < K) load_server<C, PL>(b, t.base, t.left, true, !sglobal, sr);
     __syncthreads();
     if (w >= K || t.left == 0) return;
     gather_group<C>(slots + (int64_t)w * G * C * kWave, a.N - g0, acc);
 
     float4 u[C], q[C], dq[C];
-    server_input<C, PL>(a, acc, t.base, t.left, sr, u);
+    server_input<C, PL>(b, acc, t.base, t.left, sr, u);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) q[ch] = add4(u[ch], sr.e[ch]);
     zero_past_end<C>(q, t.left);
     if (sglobal) {
-        const Row ub = row_of(a.ubuf + t.base, t.left);
+        const Row ub = row_of(b.ubuf + t.base, t.left);
 #pragma unroll
         for (int ch = 0; ch < C; ++ch) st4(ub, ch, u[ch]);
-        const double part = tile_partial<C>(a.qs, q);
-        if (lane == 0) a.spart[t.tile] = part;
+        const double part = tile_partial<C>(b.qs, q);
+        if (lane == 0) b.spart[t.tile] = part;
         return;
     }
-    WordSink sink = message_sink<QS>(a.qs, a.scodes, t.base, t.left);
-    quantize_tile<C, QS>(a.qs, lut_s, q, t.base, t.left, a.k0, a.k1, a.t, kServerStream, 0.0f, a.scodes, a.sscales,
+    WordSink sink = message_sink<QS>(b.qs, b.scodes, t.base, t.left);
+    quantize_tile<C, QS>(b.qs, lut_s, q, t.base, t.left, b.k0, b.k1, b.t, kServerStream, 0.0f, b.scodes, b.sscales,
                          sink, dq);
     sink.flush();
-    const Row e = row_of(a.e_s + t.base, t.left), x = row_of(a.x + t.base, t.left);
+    const Row e = row_of(b.e_s + t.base, t.left), x = row_of(b.x + t.base, t.left);
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        st4(e, ch, a.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
+        st4(e, ch, b.qs.ef ? sub4(q[ch], dq[ch]) : zero4());
         st4(x, ch, sub4(sr.x[ch], dq[ch]));
     }
     }
@@ -1953,13 +2003,12 @@ inline int round_waves(int N, int C, int K, size_t lds_limit, int placement)
 // flight across the GPU stay one contiguous window.
 __device__ __forceinline__ int64_t block_slot(const StepArgs& a)
 {
-    const int64_t b = blockIdx.x;
-    const int64_t R = a.xcd_run;
+    const uint32_t b = blockIdx.x, R = (uint32_t)a.xcd_run;   // a launch has at most 2^20 blocks
     if (R <= 1) return b;
-    const int64_t grp = 8 * R;
-    const int64_t g = b / grp;
-    if ((g + 1) * grp > (int64_t)gridDim.x) return b;     // the last, partial group as dealt
-    const int64_t i = b - g * grp;
+    const uint32_t grp = 8 * R;
+    const uint32_t g = b / grp;
+    if ((g + 1) * grp > gridDim.x) return b;              // the last, partial group as dealt
+    const uint32_t i = b - g * grp;
     return g * grp + (i % 8) * R + i / 8;
 }
 
