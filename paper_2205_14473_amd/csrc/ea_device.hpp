@@ -395,12 +395,15 @@ __device__ __forceinline__ float deq_of(const QDev& q, const float* lut, uint32_
 // ---------------------------------------------------------------------------
 typedef uint32_t ea_u2v __attribute__((ext_vector_type(2)));
 typedef uint32_t ea_u4v __attribute__((ext_vector_type(4)));
+typedef float ea_f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef __attribute__((address_space(1))) ea_f4u ea_global_f4;
 constexpr int kNonTemporal = 2;          // cache policy bits of the buffer builtins
 constexpr int kRawBuffer = 0x00027000;   // descriptor word 3 of a raw buffer
 
 // A span of a row: the descriptor of elements [base, min(base + span, d)).
 struct Row {
     __amdgpu_buffer_rsrc_t r;
+    const float* p;
 };
 
 // Elements of [base, base + span) that lie in a vector of d elements.
@@ -413,13 +416,20 @@ __device__ __forceinline__ int span_left(int64_t base, int64_t d, int span)
 // p: start of the row's span; left: its elements.  Both must be wave-uniform.
 __device__ __forceinline__ Row row_of(const float* p, int left)
 {
-    return Row{__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, left * 4, kRawBuffer)};
+    return Row{__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, left * 4, kRawBuffer), p};
 }
 
-// Chunk `ch` of the span, this lane's four elements.
-template <bool STREAM = true>
+// Chunk `ch` of the span, this lane's four elements.  WHOLE: the whole span lies
+// inside the vector, and a global load (4-byte alignment is enough) takes them:
+// see whole_loads.
+template <bool STREAM = true, bool WHOLE = false>
 __device__ __forceinline__ float4 ld4(const Row& row, int ch)
 {
+    if constexpr (WHOLE) {
+        const ea_global_f4* q = (const ea_global_f4*)(const ea_f4u*)(row.p + ch * kChunk + 4 * lane_id());
+        const ea_f4u v = STREAM ? __builtin_nontemporal_load(q) : *q;
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
     const ea_u4v v = __builtin_amdgcn_raw_buffer_load_b128(row.r, lane_id() * 16 + ch * (kChunk * 4), 0,
                                                            STREAM ? kNonTemporal : 0);
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));

@@ -120,6 +120,21 @@ __host__ __device__ constexpr bool half_kernel()
     return QW::fixed && !QS::fixed && PL < 0;
 }
 
+// Whether a round kernel reads spans that lie wholly inside the vector with
+// global loads, and only ragged ones through the descriptors.  The two bring
+// the same bytes, but on long rounds bound by HBM the global loads reach a
+// little more of it: 40M parameters, 8 workers, no compression 1230 -> 1110 us
+// (row lengths of a multiple of 4 KB; 1166 -> 1157 others), Example 2, 16 workers
+// 1680 -> 1625, BERT-sized 4523 -> 4478, Adam at the workers 9904 -> 9753.  Not
+// on wider tiles or the generic kernels, which are bound by their arithmetic
+// (Example 1, 2 bits in 2048-element buckets 6761 -> 6902 us, random-32 of 1024
+// 1703 -> 1746), nor with top-k on both sides (4469 -> 4522).
+template <int C, class QW, class QS>
+__host__ __device__ constexpr bool whole_loads()
+{
+    return C <= 2 && QW::fixed && !(QS::fixed && QW::kind(QDev{}) == Q_TOPK);
+}
+
 // Elements of the tile's chunk `ch` among this lane's four that lie inside d
 // (left: the tile's elements inside d).
 __device__ __forceinline__ bool inside(int left, int ch, int k)
@@ -1195,16 +1210,16 @@ __device__ __forceinline__ WorkerSpan worker_span(const StepArgs& a, const float
 }
 
 // The tile that starts at chunk ch0 of the span.
-template <int C, int PL, bool STREAM = true>
+template <int C, int PL, bool STREAM = true, bool WHOLE = false>
 __device__ __forceinline__ void load_worker(const StepArgs& a, const WorkerSpan& s, int ch0, WorkerRows<C>& r)
 {
 #pragma unroll
     for (int ch = 0; ch < C; ++ch) {
-        r.g[ch] = ld4<STREAM>(s.g, ch0 + ch);
-        r.e[ch] = ld4<STREAM>(s.e, ch0 + ch);
+        r.g[ch] = ld4<STREAM, WHOLE>(s.g, ch0 + ch);
+        r.e[ch] = ld4<STREAM, WHOLE>(s.e, ch0 + ch);
         if (placement_of<PL>(a) == AT_WORKER) {
-            r.m[ch] = ld4<STREAM>(s.m, ch0 + ch);
-            r.v[ch] = ld4<STREAM>(s.v, ch0 + ch);
+            r.m[ch] = ld4<STREAM, WHOLE>(s.m, ch0 + ch);
+            r.v[ch] = ld4<STREAM, WHOLE>(s.v, ch0 + ch);
         }
     }
 }
@@ -1311,7 +1326,7 @@ struct ServerRows {
     float4 m[C], v[C], e[C], x[C];
 };
 
-template <int C, int PL>
+template <int C, int PL, bool WHOLE = false>
 __device__ __forceinline__ void load_server(const StepArgs& a, int64_t base, int left, bool with_e, bool with_x,
                                             ServerRows<C>& r)
 {
@@ -1321,11 +1336,11 @@ __device__ __forceinline__ void load_server(const StepArgs& a, int64_t base, int
     for (int ch = 0; ch < C; ++ch) {
         r.m[ch] = r.v[ch] = r.e[ch] = r.x[ch] = zero4();
         if (placement_of<PL>(a) == AT_SERVER) {
-            r.m[ch] = ld4(m, ch);
-            r.v[ch] = ld4(v, ch);
+            r.m[ch] = ld4<true, WHOLE>(m, ch);
+            r.v[ch] = ld4<true, WHOLE>(v, ch);
         }
-        if (with_e) r.e[ch] = ld4(e, ch);
-        if (with_x) r.x[ch] = ld4(x, ch);
+        if (with_e) r.e[ch] = ld4<true, WHOLE>(e, ch);
+        if (with_x) r.x[ch] = ld4<true, WHOLE>(x, ch);
     }
 }
 
@@ -1503,16 +1518,22 @@ __device__ __forceinline__ float worker_scale(const StepArgs& a, int64_t i, bool
 // first, so the later tiles' loads are in flight while the first is
 // compressed; the codes of the tiles leave through one sink, as one piece.
 // Tile k's dequantized values go to slots + (k*G + w)*C*64.
-template <int C, int K, class QW, int PL>
+template <int C, int K, class QW, int PL, bool WHOLE>
 __device__ __forceinline__ void worker_round(const StepArgs& a, const TilePos (&tp)[K], int left,
                                              const float* lut_w, int i, float4* slots, int G, int w)
 {
     const int64_t base = tp[0].base, row = (int64_t)i * a.d;
     const WorkerSpan s = worker_span<PL>(a, a.g + row, a.e_w + row, a.m_w + row, a.v_w + row, base, left);
     WorkerRows<C> r[K];
+    if constexpr (!select_first<QW, C>()) {
+        if (WHOLE && left == K * C * kChunk) {
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if constexpr (!select_first<QW, C>()) load_worker<C, PL>(a, s, k * C, r[k]);
+            for (int k = 0; k < K; ++k) load_worker<C, PL, true, WHOLE>(a, s, k * C, r[k]);
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) load_worker<C, PL>(a, s, k * C, r[k]);
+        }
+    }
     float gs = 0.0f;
     if (has_scale<QW>(a.qw) && QW::cpb(a.qw) == 0) gs = worker_scale(a, i, base == 0);
     WordSink sink = message_sink<QW>(a.qw, a.wcodes + (int64_t)i * a.qw.words, base, left);
@@ -1712,6 +1733,7 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, co
     // rows only before that tile's arithmetic.  (With the later tiles under a
     // branch it waited for every load, and for the stores issued since,
     // before the first tile and again before the second.)
+    constexpr bool kWhole = whole_loads<C, QW, QS>();
     const int left = span_left(tile0 * C * kChunk, a.d, K * C * kChunk);
     TilePos tp[K];
 #pragma unroll
@@ -1739,13 +1761,13 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, co
     float4* slots;
     for (; g0 + G < a.N; g0 += G, buf ^= a.one_buffer ? 0 : 1) {
         slots = xfer + buf * per_buf;
-        worker_round<C, K, QW, PL>(a, tp, left, lut_w, g0 + w, slots, G, w);
+        worker_round<C, K, QW, PL, kWhole>(a, tp, left, lut_w, g0 + w, slots, G, w);
         __syncthreads();
         gather(slots, G);
         if (a.one_buffer) __syncthreads();
     }
     slots = xfer + buf * per_buf;
-    if (g0 + w < a.N) worker_round<C, K, QW, PL>(a, tp, left, lut_w, g0 + w, slots, G, w);
+    if (g0 + w < a.N) worker_round<C, K, QW, PL, kWhole>(a, tp, left, lut_w, g0 + w, slots, G, w);
     const StepArgs b = server_args(a);
     if constexpr (kSplit) {
         if constexpr (kSparse) serve_sparse<C, QS, PL>(b, tp[0], lut_s, slots, a.N - g0, acc[0]);
@@ -1754,7 +1776,10 @@ __device__ __forceinline__ void round_tiles(const StepArgs& a, int64_t tile0, co
     } else {
     const TilePos t = tile_of<C>(tile0, w < K ? w : 0, left);
     ServerRows<C> sr;
-    if (w < K) load_server<C, PL>(b, t.base, t.left, true, !sglobal, sr);
+    if (w < K) {
+        if (kWhole && t.left == C * kChunk) load_server<C, PL, kWhole>(b, t.base, t.left, true, !sglobal, sr);
+        else load_server<C, PL>(b, t.base, t.left, true, !sglobal, sr);
+    }
     __syncthreads();
     if (w >= K || t.left == 0) return;
     gather_group<C>(slots + (int64_t)w * G * C * kWave, a.N - g0, acc);
