@@ -571,7 +571,7 @@ int ea_server_compress(const ea_config_t* c, int64_t t, const float* u, float* e
     hipError_t e = hipSuccess;
     if (p.sglobal) {
         a.spart = (double*)((char*)workspace + p.off_spart);
-        a.snp = ea::block_parts(p.ntiles);
+        a.snp = p.ntiles;
         a.from_parts = p.ntiles <= kPartsInline ? 1 : 0;
         e = ea::launch_server_partials(a, p.C, s);
         if (e == hipSuccess && !a.from_parts) e = ea::launch_finalize(a.spart, a.snp, p.qs.norm, c->d, scales, 1, 1, s);

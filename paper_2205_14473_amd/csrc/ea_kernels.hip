@@ -41,21 +41,20 @@ __global__ __launch_bounds__(kBlock) void worker_partials_kernel(StepArgs args, 
     store_block_part(part, a.qw.norm, a.wpart + i * a.wnp + blockIdx.x);
 }
 
-// Partial norms of q = u + e_s, one per block of tiles (one-bucket Q_s, split
-// call).
+// Partial norms of q = u + e_s, one per tile as the fused round leaves them
+// (one-bucket Q_s, split call): the same partials, added in the same order,
+// make the split call's scale the round's to the last bit.
 template <int C>
 __global__ __launch_bounds__(kBlock) void server_partials_kernel(StepArgs a)
 {
     TilePos t;
-    double part = 0.0;
-    if (tile_pos<C>(a, t)) {
-        const Row u = row_of(a.ubuf + t.base, t.left), e = row_of(a.e_s + t.base, t.left);
-        float4 q[C];
+    if (!tile_pos<C>(a, t)) return;
+    const Row u = row_of(a.ubuf + t.base, t.left), e = row_of(a.e_s + t.base, t.left);
+    float4 q[C];
 #pragma unroll
-        for (int ch = 0; ch < C; ++ch) q[ch] = add4(ld4<false>(u, ch), ld4<false>(e, ch));
-        part = tile_partial<C>(a.qs, q);
-    }
-    store_block_part(part, a.qs.norm, a.spart + blockIdx.x);
+    for (int ch = 0; ch < C; ++ch) q[ch] = add4(ld4<false>(u, ch), ld4<false>(e, ch));
+    const double part = tile_partial<C>(a.qs, q);
+    if (lane_id() == 0) a.spart[t.tile] = part;
 }
 
 // Reduce partials to one scale per vector: block v handles part[v*nparts ..

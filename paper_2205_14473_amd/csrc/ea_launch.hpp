@@ -92,8 +92,8 @@ hipError_t launch_worker_partials(const StepArgs& a, int C, int nworkers, hipStr
 hipError_t launch_server_partials(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_finalize(const double* part, int64_t nparts, int32_t norm, int64_t n, float* out,
                            int64_t out_stride, int nvec, hipStream_t s);
-// Partial norms of one vector of ntiles tiles: one per block of kWavesPerBlock
-// tiles from the partials kernels, one per tile from the fused round.
+// Partial norms of a worker's vector of ntiles tiles: one per block of
+// kWavesPerBlock tiles (of the server's vector there is one per tile).
 inline int64_t block_parts(int64_t ntiles) { return (ntiles + kWavesPerBlock - 1) / kWavesPerBlock; }
 hipError_t launch_worker(const StepArgs& a, int C, hipStream_t s);
 hipError_t launch_aggregate(const StepArgs& a, int C, hipStream_t s);

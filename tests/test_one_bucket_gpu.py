@@ -43,3 +43,42 @@ def test_one_bucket_worker_with_bucketed_server():
         for t in range(1, 3):
             pair.step(t, (1e-2 * rng.standard_normal((2, d))).astype(np.float32))
         pair.check_tie_budget()
+
+
+@pytest.mark.parametrize("side", ["worker", "server"])
+@pytest.mark.parametrize("tiles", [4, 1024])
+def test_round_and_split_calls_add_the_norm_in_one_order(tiles, side):
+    """The round gives what the four calls give, to the last bit of a scale: here
+    the binary64 sum of the tiles' partial norms lies on the boundary between
+    two binary32 scales, and adding tiles 0 to 3 one after the other gives the
+    lower one, in pairs the upper."""
+    import paper_2205_14473_amd as E
+    from paper_2205_14473_amd.state import allocate, init_state
+    d = 512 * tiles
+    big = torch.zeros(d)
+    big[0], big[1] = 2.0 ** 24, 1.0                     # a tie between two binary32 sums
+    big[[512, 1024, 1536]] = 1.5 * 2.0 ** -30           # three eighths of a binary64 last place each
+    none = E.Quant(kind=E.EA_Q_NONE, error_feedback=1)
+    sign = E.Quant(kind=E.EA_Q_SCALED_SIGN, bucket=0, error_feedback=1)
+    cfg = E.Config(d=d, N=1, placement=E.EA_ADAM_AT_WORKER, beta1=0.9, beta2=0.999, lr=1e-3, eps=0.0, seed=1,
+                   qw=sign if side == "worker" else none, qs=sign if side == "server" else none)
+    got = []
+    for split in (False, True):
+        rb = allocate(cfg, with_u=True)
+        init_state(cfg, rb)
+        rb.g.zero_()
+        (rb.e_w[0] if side == "worker" else rb.e_s).copy_(big)
+        if split:
+            some = side == "worker"
+            E.ea_worker_compress(cfg, 0, 1, rb.g[0], rb.e_w[0], rb.m_w[0], rb.v_w[0], rb.wcodes[0],
+                                 rb.wscales[0] if some else None, rb.workspace)
+            E.ea_server_aggregate_adam(cfg, 1, rb.wcodes, rb.wscales if some else None, rb.m, rb.v, rb.u)
+            E.ea_server_compress(cfg, 1, rb.u, rb.e_s, rb.scodes, None if some else rb.sscales, rb.workspace)
+            E.ea_worker_apply(cfg, rb.scodes, None if some else rb.sscales, rb.x)
+        else:
+            E.ea_step(cfg, 1, **rb.step_args())
+        torch.cuda.synchronize()
+        scale = rb.wscales if side == "worker" else rb.sscales
+        got.append([t.cpu().numpy().copy() for t in (scale, rb.e_w, rb.e_s, rb.x)])
+    for name, a, b in zip(("scale", "e_w", "e_s", "x"), *got):
+        assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), (name, a.ravel()[:3], b.ravel()[:3])
