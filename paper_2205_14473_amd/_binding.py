@@ -112,7 +112,8 @@ def _load_torch():
     global _torch, _F32, _U64, _raw_stream, _device
     import torch
     _F32, _U64 = torch.float32, torch.uint64
-    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+    # not in every torch: one built without GPU support has no such symbol
+    _raw_stream, _device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
     _torch = torch
 
 
@@ -137,7 +138,7 @@ def _stream(stream):
     if stream is None:
         if _torch is None:
             _load_torch()
-        return _raw_stream(_device())
+        return _raw_stream(_device()) if _raw_stream else _torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
