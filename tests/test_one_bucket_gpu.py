@@ -82,3 +82,36 @@ def test_round_and_split_calls_add_the_norm_in_one_order(tiles, side):
         got.append([t.cpu().numpy().copy() for t in (scale, rb.e_w, rb.e_s, rb.x)])
     for name, a, b in zip(("scale", "e_w", "e_s", "x"), *got):
         assert np.array_equal(a.view(np.uint32), b.view(np.uint32)), (name, a.ravel()[:3], b.ravel()[:3])
+
+
+@pytest.mark.parametrize("mode", ["step", "split"])
+@pytest.mark.parametrize("what", ["zero", "subnormal", "infinite"])
+@pytest.mark.parametrize("qw,qs", [(SIGN, SIGN), (STOCH(4, O.SCALE_L2), STOCH(2, O.SCALE_MAX)), (DET(3), DET(2)),
+                                   (DET(6), STOCH(8, O.SCALE_L2)),
+                                   (STOCH(2, O.SCALE_MAX), qfields(O.Q_SCALED_SIGN, 1, O.SCALE_L1, bucket=1024))])
+def test_one_bucket_scale_zero_subnormal_or_infinite(qw, qs, what, mode):
+    """Given scales that send the whole vector as zeros or need the 2^64
+    pre-scale, on the specialized kernels, the generic one (server buckets of
+    1024) and below and above 512 tiles.  Infinite: magnitudes whose squares
+    overflow, then an infinite gradient as well, which every norm follows."""
+    rng = np.random.default_rng(3)
+    N = 3
+    for d in (512 * 3 + 65, 513 * 512 + 1):
+        pair = Pair(d, N, qw, qs, O.ADAM_AT_SERVER, seed=6, eps=0.0)
+        sgn = rng.choice(np.array([-1.0, 1.0], np.float32), size=(N, d))
+        g = np.zeros((N, d), np.float32)
+        if what == "subnormal":
+            g = sgn * (rng.integers(0, 215, (N, d)) * 2.0 ** -149).astype(np.float32)
+        elif what == "infinite":
+            g = sgn * rng.uniform(2.0, 3.0, (N, d)).astype(np.float32) * np.float32(1e38)
+        for t in range(1, 3):
+            if what == "infinite" and t == 2:
+                g[:, 7] = np.inf
+            pair.step(t, g)
+            got = pair.rb.wscales.cpu().numpy()[:, 0]
+            if what != "infinite":
+                assert (got < 2.0 ** -126).all()
+                assert what == "subnormal" or (got == 0).all()
+        if what == "infinite":
+            assert np.isinf(got).all()
+        pair.check_tie_budget()
