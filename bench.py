@@ -350,7 +350,7 @@ def main():
             "traffic": (traffic_from_profile(args.workload, args.placement, args.call)
                         if args.call in ("step", "split") else None),
             "kernel": ("worker_kernel x N, aggregate_kernel, server_kernel, apply_kernel" if args.call == "split"
-                       else "step_kernel (whole tiles + ragged tail)"),
+                       else "step_kernel"),
             "algorithmic_bytes_per_round": alg,
             "bytes_per_param": round(alg / cfg.d, 2)}
     line = {

@@ -21,7 +21,8 @@
  *   - Device pointers must be 4-byte aligned (else EA_ERR_ALIGN).  Every
  *     layout runs on the same kernels; rows whose byte length is a multiple of
  *     128 share no cache line between tiles and are a little faster (25.6M
- *     parameters, 8 workers: an odd count 0.605 ms, a multiple of 32 0.574 ms).
+ *     parameters, 8 workers: an odd count 0.64 to 0.67 ms, a multiple of 32
+ *     0.62 to 0.63 ms).
  *   - Calls that share buffers must be ordered by the caller (same stream).
  *
  * Wire format of a message (the paper defines none)

@@ -113,9 +113,8 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
 }
 
 // The key made opaque at the start of a tile, so that the scalar unit forms the
-// 18 round keys anew for each tile: held across tiles and phases, they pushed
-// other scalars out into vector lanes (62 -> 47 spilled in the BERT-sized
-// round's kernel).
+// 18 round keys anew for each tile: held across tiles and phases they push
+// other values out (95 -> 89 VGPRs in the BERT-sized round's kernel).
 __device__ __forceinline__ void renew_key(uint32_t& k0, uint32_t& k1)
 {
     asm volatile("" : "+s"(k0), "+s"(k1));

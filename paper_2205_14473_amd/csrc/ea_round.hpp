@@ -2050,11 +2050,12 @@ __device__ __forceinline__ int64_t block_slot(const StepArgs& a)
 // workers: 5.7-5.9 TB/s, as much as a plain e += g moves), by launch and
 // memory latency where it is small.  Against separate kernels for whole tiles
 // of aligned rows and for everything else: 25,557,031 parameters (odd), 8
-// workers, stochastic 4-bit 1723 -> 605 us (1.97 -> 5.6 TB/s); 2,762,241
+// workers, stochastic 4-bit 1780 -> 641 us (1.9 -> 5.3 TB/s); 2,762,241
 // parameters, 8 workers, one bucket 298 -> 162 us; 1,049,627 parameters, 32
 // workers, sign 439 -> 94 us; 6,624 parameters, 8 workers, without
 // compression 44 -> 9.7 us (one launch instead of two with a fork and a join);
-// aligned rounds of 11M parameters and more within 1%.
+// aligned rounds of 11M parameters and more from 3% slower (no compression,
+// Adam at the workers) to 9% faster.
 template <int C, class QW, class QS, int PL, int MW = 0>
 __global__ __launch_bounds__(max_round_waves(C) * kWave,
                              MW > 0 ? MW : round_min_waves(C, PL == AT_SERVER)) void step_kernel(StepArgs args)

@@ -10,9 +10,8 @@ namespace ea {
 
 namespace {
 
-// Two waves per SIMD (up to 256 VGPRs): capped at 168 for a third wave, these
-// kernels spill 30 to 70 VGPRs and run up to 1.6x slower on a BERT-sized
-// round.
+// Two waves per SIMD at least: the stochastic ones take 166 to 173 VGPRs, 168
+// leaving room for a third, the sign one 93; none spills VGPRs.
 #ifndef EA_SYM_C8_MIN_WAVES
 #define EA_SYM_C8_MIN_WAVES 2
 #endif

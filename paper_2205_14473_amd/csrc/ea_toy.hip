@@ -45,7 +45,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const void* p, int64_t 
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(bytes < cap ? bytes : cap), kRawBuffer);
 }
 
-// Bound by the read of A (d = 8192: 6.4 TB/s); at d = 500 by one memory
+// Bound by the read of A (d = 8192: 38 us, 7.0 TB/s, A fitting the memory-side
+// cache in part); at d = 500 by one memory
 // latency, so the loads of up to four 256-element chunks of the row go out
 // together.  A product of two binary32 values is exact in binary64.
 __global__ __launch_bounds__(kResWaves * kWave) void toy_residual_kernel(int64_t d, const float* __restrict__ A,
@@ -178,8 +179,8 @@ struct ToyArgs {
 // loads are in flight are as many as paid: at two tiles two sets of one (one
 // set of three 99 us a step at d = 8192, three sets of one 94, against 92), at
 // four one set of two.  Measured, 10 workers, a whole step, before and after:
-// d = 500 22.4 -> 13.9 us, 4096 122 -> 39.6 us, 8192 334 -> 92 us (A read twice
-// 5.9 TB/s), 16384 1025 -> 394 us (5.5 TB/s), 40000 4.70 -> 2.37 ms (5.4 TB/s);
+// d = 500 22.4 -> 13.9 us, 4096 122 -> 39.6 us, 8192 334 -> 92-101 us (A read
+// twice 5.3-5.9 TB/s), 16384 1025 -> 394 us (5.5 TB/s), 40000 4.70 -> 2.37 ms (5.4 TB/s);
 // 20 workers (two passes) at d = 1557 103 -> 26 us.
 template <int CT, int SETS, int AHEAD, bool ROUND>
 __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
@@ -290,7 +291,8 @@ __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
         // After the sums, thread (o, column) holds output o of the pass.  Its
         // rows and the server's (only this block writes them) are loaded here
         // and arrive during the reduction; loaded before the sums they took
-        // registers from the groups in flight.
+        // registers from the groups in flight.  (The 64-column kernel spills 11
+        // VGPRs to scratch all the same, once a pass outside the sums.)
         const int o = (int)threadIdx.x / COLS;
         const int64_t wrow = (int64_t)(g0 + (o < nw ? o : 0)) * d + (in ? col : d - 1);
         float e0 = 0.0f, m0 = 0.0f, v0 = 0.0f;
@@ -399,11 +401,13 @@ __global__ __launch_bounds__(kTRWaves * kWave) void toy_round_kernel(ToyArgs a)
 
     // The block's share of ||grad F||^2.  The last block to get here adds the
     // shares: lane l those of blocks l, l+64, ... in order (loaded side by
-    // side), then the wave's sum.  Share and loads are device-coherent by
-    // themselves (agent-scope atomics, written through and read past the L2s),
-    // so all that is needed is that the share has arrived before the count:
-    // the wait.  (A release fence would write back the XCD's whole L2, an
-    // acquire drop it.)
+    // side), then the wave's sum.  The order rests on this chip's rules, not on
+    // the memory model, in which relaxed atomics publish nothing: agent-scope
+    // stores are written through to where every XCD's agent-scope loads read,
+    // past the L2s, and the store has completed there when vmcnt is 0, so the
+    // wait puts the share before the count; the loads depend on the count.
+    // (What the model asks for, a release fence, would write back the XCD's
+    // whole L2, and its acquire drop it.)
     if (w == norm_wave(a.N < kTRWorkers ? a.N : kTRWorkers) && a.grad_sq != nullptr) {
         const double sq = wave_sum(norm_sq);
         unsigned long long* bits = reinterpret_cast<unsigned long long*>(a.part);
@@ -440,10 +444,11 @@ int toy_cols(int64_t d)
 }
 
 // The two launches use r (d doubles), a partial norm per column block and the
-// counter of blocks done (a 32-bit word).  The size that callers are told is
-// the ABI's own: with 64-column blocks just that and a counter for each (as
-// 32-bit words), with 32-column blocks up to eight sets of sixteen 64-column
-// sums for each 64 columns besides, many times what is used.
+// counter of blocks done (a 32-bit word): 70 KB at d = 8192.  The size that
+// callers are told stays the one they always were: r, a norm for each 64 columns, a
+// 32-bit word for each and one more, and, while there are at most 512 groups of 64 columns
+// (d <= 32768), two to eight sets of sixteen 64-column sums for each; never less than
+// is used, since 32-column blocks end at d = 16320.
 int64_t toy_workspace_bytes(int64_t d)
 {
     const int64_t cols64 = (d + kWave - 1) / kWave;

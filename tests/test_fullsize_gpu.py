@@ -102,13 +102,11 @@ def test_full_size_sampled(key, placement, T):
 @pytest.mark.parametrize("tail", [76, 77], ids=["aligned", "unaligned"])
 def test_launch_in_pieces(placement, tail):
     """Launches of more than 2^20 blocks are issued in pieces.  Scaled sign on
-    256-element buckets with one worker: with d = 2^29 + 512 + 76 (rows
-    16-byte aligned) the whole-tile kernel takes two tiles per block, 2^20 + 1
-    blocks (two pieces), and the checked one the ragged tile; with d = 2^29 +
-    512 + 77 (unaligned rows) the checked kernel takes every tile, one per
-    block (three pieces).  The segments on both sides of the piece boundaries
-    at elements 2^28 and 2^29, the first and the last are checked against the
-    oracle after every step."""
+    256-element buckets with one worker, two tiles per block: d = 2^29 + 512 + 76
+    (rows 16-byte aligned) and d = 2^29 + 512 + 77 (unaligned rows) take 2^20 + 2
+    blocks, the last with one ragged tile: two pieces.  The segments on both sides of the piece boundary at
+    element 2^29 and of its half, the first and the last are checked against
+    the oracle after every step."""
     sign = W.SIGN1(256)
     d = (1 << 29) + 2 * 256 + tail
     w = W.Workload("pieces", f"d=2^29+{512 + tail} N=1, sign 256", d, 1, sign, sign, 2, 31, "student_t")

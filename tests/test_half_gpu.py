@@ -4,9 +4,8 @@ worker quantizer of those tables (scaled sign; stochastic 1/2/4/8-bit with L2
 or max-norm scale; top-k; random-k; Example 1 with 2 or 3 bits) at every
 bucket size 256 to 2048, paired with a different server quantizer whose bucket
 is no larger, in both placements; Example 2 and full precision (no bucket) at
-the tile size of the server's bucket.  Sizes hold several whole tiles (the
-specialized launch) and a ragged tail (the generic edge launch); one-chunk
-tiles go two to a block, so odd and even tile counts both occur."""
+the tile size of the server's bucket.  Sizes hold several whole tiles and a
+ragged last one, all in one launch; one-chunk tiles go two to a block, so odd and even tile counts both occur."""
 import numpy as np
 import pytest
 

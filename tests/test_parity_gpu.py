@@ -153,7 +153,7 @@ def test_zero_gradients_give_zero_scales():
         pair.step(t, g)
 
 
-# Lean whole-tile kernels take two consecutive tiles per block: odd and even
+# Lean kernels take two consecutive tiles per block: odd and even
 # tile counts, with and without a ragged tail, a single tile, and more workers
 # than waves per block (double-buffered handoff).
 @pytest.mark.parametrize("d", [512 * 41 + 384, 512 * 41, 512 * 42, 512 + 100, 512, 1024 * 3])
@@ -283,7 +283,7 @@ def test_one_worker_two_tile_blocks(name, q, placement, d):
 @pytest.mark.parametrize("placement", [O.ADAM_AT_SERVER, O.ADAM_AT_WORKER], ids=["server", "worker"])
 def test_xcd_runs_cover_every_tile(placement):
     """Rows whose byte length is not a multiple of 128 (d = 8 mod 32), one
-    2048-element tile per block: the whole-tile launch deals each whole group
+    2048-element tile per block: the launch deals each whole group
     of 128 blocks XCD-major.  300 whole tiles make two whole groups and a
     partial one, plus the ragged tile; every element is checked."""
     d, N = 2048 * 300 + 8, 8
@@ -337,9 +337,8 @@ def test_subnormal_learning_rate(kind):
 
 
 def test_full_precision_messages_unaligned():
-    """Messages sent as raw values go out as float4 only when the message
-    buffers are 16-byte aligned: an 8-byte aligned worker message array takes
-    the checked kernels and gives the same results."""
+    """Messages sent as raw values go out sixteen bytes a lane also from message
+    buffers that are only 8-byte aligned, with the same results."""
     d, N = 512 * 6 + 64, 4
     q = qfields(O.Q_NONE)
     for shift in (0, 1):

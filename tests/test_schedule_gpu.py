@@ -27,7 +27,7 @@ SCHEDS = {
     "step_decay": dict(kind=O.SCHED_STEP_DECAY, alpha=1e-3, factor=0.2, period=2),
 }
 CASES = {
-    # specialized whole-tile kernels (two tiles per block) plus the ragged tail
+    # fully specialized kernels (two tiles per block), a ragged last tile
     "bert_like": (512 * 5 + 300, 16, STOCH(4, O.SCALE_L2, 512), STOCH(4, O.SCALE_L2, 512), O.ADAM_AT_SERVER),
     # generic kernels, Adam at the workers
     "generic_worker": (3000, 4, qfields(O.Q_DET_UNIFORM, 3, bucket=256), SIGN(512), O.ADAM_AT_WORKER),

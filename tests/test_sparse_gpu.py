@@ -1,7 +1,7 @@
 """GPU parity of the Definition 3 sparsifiers (top-k and random-k per bucket)
 against the oracle: kept masks and kept values bit-exact, state within the
-float tolerance, after every step of a trajectory.  Covers the specialized
-whole-tile kernels (bucket 512, Adam at the server), the generic kernels, the
+float tolerance, after every step of a trajectory.  Covers the fully specialized
+kernels (bucket 512, Adam at the server), the generic kernels, the
 split calls (which decode the messages), ragged and tiny sizes, equal keys at
 the threshold, and keep at its limits."""
 import numpy as np
@@ -49,7 +49,7 @@ def _run(d, N, qw, qs, placement, T, gen="student_t", seed=5, split=False, **hp)
 @pytest.mark.parametrize("d", [512 * 41 + 384, 512 * 42, 512 * 41, 512 + 100, 300])
 def test_lean_kernels(kind, d):
     """Bucket 512, Adam at the server, 16 workers: the specialized two-tile
-    kernels plus the edge kernel of a ragged tail."""
+    kernels, with whole and ragged last tiles."""
     q = SPARSE[kind](16, 512)
     _run(d, 16, q, q, O.ADAM_AT_SERVER, T=4)
 

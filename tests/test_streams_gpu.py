@@ -1,6 +1,5 @@
-"""The ragged last tile of a fused round may run on the library's side stream,
-forked from the caller's stream and joined back to it.  These tests issue such
-rounds from two host threads at once, each on its own stream, and check that
+"""Rounds on streams of the caller's: issued from two host threads at once, each
+on its own stream, rounds share nothing inside the library.  These tests check that
 every message and state array equals that of the same rounds issued one after
 the other on one stream; and that work queued on the caller's stream right
 after a round sees all of its results."""
@@ -24,7 +23,7 @@ from parity_util import configs, qfields  # noqa: E402
 
 SIGN = lambda b: qfields(O.Q_SCALED_SIGN, 1, O.SCALE_L1, 1, b)  # noqa: E731
 STOCH4 = qfields(O.Q_STOCH_UNIFORM, 4, O.SCALE_L2, 1, 512)
-# whole tiles plus a ragged one, few enough blocks that the side stream is taken
+# whole tiles plus a ragged one
 SHAPES = [
     (2048 * 37 + 1500, 8, SIGN(2048), SIGN(2048)),      # 8-chunk tiles, ResNet-18-like
     (512 * 301 + 77, 16, STOCH4, STOCH4),               # two-tile blocks, an odd tile count

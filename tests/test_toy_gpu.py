@@ -197,7 +197,7 @@ def test_toy_step_optional_outputs_change_nothing():
         assert torch.equal(getattr(a, k).view(torch.uint8), getattr(b, k).view(torch.uint8)), k
 
 
-@pytest.mark.parametrize("d,N", [(500, 10), (300, 16)], ids=["split-rows", "one-split"])
+@pytest.mark.parametrize("d,N", [(500, 10), (300, 16)], ids=["one-pass", "two-passes"])
 def test_toy_steps_replayed_from_a_graph(d, N):
     """Five toy steps captured into a HIP graph (both launches of every step;
     the round's counters are cleared by a kernel, not a memset) and replayed
@@ -247,7 +247,7 @@ def test_toy_steps_replayed_from_a_graph(d, N):
         assert torch.equal(gs, want_gs), rep
 
 
-@pytest.mark.parametrize("d,N", [(500, 10), (777, 31), (65, 2)], ids=["split-rows", "two-passes", "ragged"])
+@pytest.mark.parametrize("d,N", [(500, 10), (777, 31), (65, 2)], ids=["one-pass", "three-passes", "ragged"])
 def test_toy_grad_equals_fused_step_gradients(d, N):
     """ea_toy_grad and ea_toy_step (through g_out) sum in the same order: the
     same gradients bit for bit, and the same ||grad F||^2."""
