@@ -250,6 +250,23 @@ int step_waves(const StepArgs& a, int C, int K, const Special* sp, const SymKern
 #define EA_XCD_RUN 16
 #endif
 
+// LDS that a block of G waves asks for at least.  Full-precision rounds have no
+// arithmetic to hide, and the more of their blocks a CU holds the less of HBM
+// they reach: two 8-wave blocks or their like, and not a third beside two that
+// end.  With Adam at two workers and more at any size (8 workers, 1M parameters
+// 51.6 -> 50.9 us, 16M 913 -> 901, 40M 2128 -> 2086; one worker, 355M 3264 ->
+// 3308); with Adam at the server, where a
+// block's waves wait longer for each other, once the rows are long (8 workers,
+// 40M 1138 -> 1090, 4 workers, 110M 1948 -> 1891, but 4M 125.7 -> 128.4).  Blocks
+// of more than 8 waves fill a CU by themselves, and the kernels with codes need
+// the others (Example 2, 8 workers, 40M 941 -> 1273).
+size_t least_lds(const StepArgs& a, int C, int G)
+{
+    const bool full = a.qw.kind == Q_NONE && C == 2 && G <= 8;
+    const bool pays = a.placement == AT_WORKER ? a.N > 1 : a.N * a.d >= (int64_t)1 << 28;
+    return full && pays ? (size_t)G * 8000 : 0;
+}
+
 // One dispatch covers at most 2^32 - 1 work-items, and the fused kernels run
 // up to four threads per element (one-chunk tiles, 16 waves, one tile per
 // block), so a round is launched in pieces of at most this many blocks (2^30
@@ -276,7 +293,8 @@ hipError_t launch_step(const StepArgs& a, int C, hipStream_t s)
     b.one_buffer = bufs == 1 ? 1 : 0;
     b.xcd_run = (a.d * 4) % 128 != 0 && K == 1 ? EA_XCD_RUN : 1;
     const dim3 block((unsigned)(G * kWave));
-    const size_t lds = round_lds_bytes(a.N, C, G, K, bufs);
+    size_t lds = round_lds_bytes(a.N, C, G, K, bufs);
+    if (hk && lds < least_lds(a, C, G)) lds = least_lds(a, C, G);
     const int64_t nblocks = (a.ntiles + K - 1) / K;
     for (int64_t b0 = 0; b0 < nblocks; b0 += kMaxLaunchBlocks) {
         const dim3 grid((unsigned)(nblocks - b0 < kMaxLaunchBlocks ? nblocks - b0 : kMaxLaunchBlocks));

@@ -2054,8 +2054,8 @@ __device__ __forceinline__ int64_t block_slot(const StepArgs& a)
 // parameters, 8 workers, one bucket 298 -> 162 us; 1,049,627 parameters, 32
 // workers, sign 439 -> 94 us; 6,624 parameters, 8 workers, without
 // compression 44 -> 9.7 us (one launch instead of two with a fork and a join);
-// aligned rounds of 11M parameters and more from 3% slower (no compression,
-// Adam at the workers) to 9% faster.
+// aligned rounds of 11M parameters and more from 2% slower (sign in
+// 256-element buckets) to 9% faster.
 template <int C, class QW, class QS, int PL, int MW = 0>
 __global__ __launch_bounds__(max_round_waves(C) * kWave,
                              MW > 0 ? MW : round_min_waves(C, PL == AT_SERVER)) void step_kernel(StepArgs args)
